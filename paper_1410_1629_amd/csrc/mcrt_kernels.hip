@@ -31,6 +31,7 @@
 #include "mcrt_attached.hpp"
 #include "mcrt_host.hpp"
 #include "mcrt_lane.hpp"
+#include "mcrt_stage.hpp"
 
 namespace mcrt {
 
@@ -150,9 +151,20 @@ __device__ __forceinline__ unsigned long long* wave_reservoir(unsigned long long
 // ---------------------------------------------------------------------------
 // Device memory accessors.
 
-template <typename R, int GK, bool INST>
+// The packages a lane machine resumes: lists that the staged kernels left
+// (list n holds counts[n] packages; the first one shorter than min_n is the
+// one they stopped at, or list n_lists - 1).
+struct StageTail {
+  const StagePkg* pkg;
+  const unsigned long long* counts;
+  unsigned long long min_n;
+  int n_lists;
+};
+
+template <typename R, int GK, bool INST, bool RES = false>
 struct LifeMem {
   static constexpr int kGrid = GK;
+  static constexpr bool kResume = RES;
   // the full variant: instruments other than frames (SED, camera) and the
   // optics and absorbed-tally gradients; the lean one compiles them out
   static constexpr bool kInst = INST;
@@ -173,6 +185,13 @@ struct LifeMem {
   long long* sidx;
   double* sval;
   int dbase;
+  // packages to resume (RES)
+  const StagePkg* res_pkg = nullptr;
+  unsigned long long res_n = 0;
+  int res_events = 0;
+  __device__ unsigned long long resume_count() const { return res_n; }
+  __device__ const StagePkg& resume_pkg(unsigned long long i) const { return res_pkg[i]; }
+  __device__ int resume_events() const { return res_events; }
   __device__ void stage_clear(int b) {
     dbase = kDepPer * __lane_id() + kBlockWalk * b;
 #pragma unroll
@@ -296,14 +315,21 @@ struct PeelMem {
 // gradients (INST).  Every variant asks for two wavefronts per SIMD, which
 // its register use could otherwise just miss (one accumulation register
 // beyond 256 halves the occupancy).
-template <typename R, bool ADJ, int GK, bool INST>
-__device__ __forceinline__ void life_body(const RunParams& P) {
+template <typename R, bool ADJ, int GK, bool INST, bool RES = false>
+__device__ __forceinline__ void life_body(const RunParams& P, const StageTail* tail = nullptr) {
   __shared__ unsigned long long slots[kWavesPerBlock][2], job_slots[kWavesPerBlock][2];
   __shared__ long long dep_idx[kWavesPerBlock][64 * kDepPer];
   __shared__ double dep_val[kWavesPerBlock][64 * kDepPer];
   const int wave = threadIdx.x / 64;
-  LifeMem<R, GK, INST> M{static_cast<const R*>(P.rho), P, wave_reservoir(slots), wave_reservoir(job_slots),
-                         dep_idx[wave], dep_val[wave], 0};
+  LifeMem<R, GK, INST, RES> M{static_cast<const R*>(P.rho), P, wave_reservoir(slots), wave_reservoir(job_slots),
+                              dep_idx[wave], dep_val[wave], 0};
+  if constexpr (RES) {
+    int n = 0;
+    while (n + 1 < tail->n_lists && tail->counts[n] >= tail->min_n) ++n;
+    M.res_pkg = tail->pkg;
+    M.res_n = tail->counts[n];
+    M.res_events = n;
+  }
   Lane<R> L;
   lane_init(L);
   int staged = 0;  // walk blocks of deposits staged in LDS (wavefront-uniform)
@@ -363,6 +389,13 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))
   life_body<double, ADJ, GK, INST>(P);
 }
 
+// The rest of the lives of the packages the staged kernels left.
+template <typename R, bool ADJ, int GK, bool INST>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) k_tail(const RunParams P,
+                                                                                         const StageTail tail) {
+  life_body<R, ADJ, GK, INST, true>(P, &tail);
+}
+
 template <typename R, int GK>
 __global__ void __launch_bounds__(kBlock) k_trace(const TraceParams P) {
   __shared__ unsigned long long slots[kWavesPerBlock][2];
@@ -404,6 +437,299 @@ __global__ void __launch_bounds__(kBlock) k_peel(const PeelParams P) {
       if (L.ry.active) peel_step(L, P, M);
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// The life cycle in stages (mcrt_stage.hpp): k_emit, then per scattering
+// order k_count, a scan, k_move, k_leg and k_event, over dense lists of
+// packages.
+
+// What k_leg reaches.
+template <typename R, int GK, bool LUT>
+struct LegMem {
+  static constexpr int kGrid = GK;
+  static constexpr bool kLut = LUT;
+  const R* __restrict__ rho_;
+  const int* lut = nullptr;
+  int o1 = 0, o2 = 0;
+  __device__ R rho(int c) const { return rho_[c]; }
+  __device__ int lut_addr(const int i[3]) const { return lut[i[0] + 1] + lut[o1 + i[1]] + lut[o2 + i[2]]; }
+  __device__ void fill_lut(int* l, const GridDev& G) {  // by the whole workgroup; the launch checks the size
+    const int tot = lut_cells(G);
+    for (int t = (int)threadIdx.x; t < tot; t += (int)blockDim.x) l[t] = lut_entry(G, t);
+    lut = l;
+    o1 = lut_first(G, 1) + 1;
+    o2 = lut_first(G, 2) + 1;
+    __syncthreads();
+  }
+};
+
+// A wavefront's supply of packages: the next 64 records of the list wait in
+// LDS, fetched by all lanes at once, so that a refill of idle lanes does not
+// wait for the counter and the records.  The list is cut into one slice per
+// XCD; a wavefront takes runs of 64 from its own XCD's slice (workgroups go
+// to the XCDs in turn), then from the others'.  Every member is
+// wavefront-uniform.
+struct PkgFeed {
+  StagePkg* buf;  // [64] in LDS
+  unsigned long long base = 0;
+  int have = 0, used = 0, tried = 0;
+  bool empty = false;
+  __device__ void more(const StageParams& S, unsigned long long count) {
+    have = used = 0;
+    while (have == 0 && tried < kXcds) {
+      const int slice = (int)((blockIdx.x + (unsigned)tried) % kXcds);
+      const unsigned long long hi = count * (slice + 1) / kXcds;
+      unsigned long long b = 0;
+      if (__lane_id() == 0) b = atomicAdd(S.next + slice, 64ull);
+      base = count * slice / kXcds + shfl_u64(b, 0);
+      if (base < hi)
+        have = hi - base < 64 ? (int)(hi - base) : 64;
+      else
+        ++tried;
+    }
+    empty = have == 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if ((int)__lane_id() < have) buf[__lane_id()] = S.in[base + __lane_id()];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  // Hands records to the lanes that want one (want: cleared where one came);
+  // p and q receive the record and its place.
+  __device__ void take(const StageParams& S, unsigned long long count, bool& want, StagePkg& p, unsigned& q) {
+    unsigned long long need = __ballot(want);
+    while (need && !empty) {
+      if (used == have) {
+        more(S, count);
+        continue;
+      }
+      const int rank = __popcll(need & ((1ull << __lane_id()) - 1ull));
+      const int n = min((int)__popcll(need), have - used);
+      if (want && rank < n) {
+        p = buf[used + rank];
+        q = (unsigned)(base + used + rank);
+        want = false;
+      }
+      used += n;
+      need = __ballot(want);
+    }
+  }
+};
+
+// Order n's legs.  The walk's 4-byte gathers bound it: each crossing is a
+// request of its own lane to the L1, where a line rarely lasts (a thousand
+// walkers per compute unit against 32 KB), so 0.5-0.8 requests per crossing
+// go on to the L2 (2.65e11 per second where they hit) and one per brick
+// entered past it (8.0e10 per second from the MALL, 5.5e10 from HBM).  On the
+// spiral that model gives 5.6 ps per crossing for packages in any order, and
+// the first order's legs take 5.7.  In order of place a third of the misses
+// go.  Forward life cycle, lane machine -> stages: spiral (1e7 packages, no
+// tally) 51.4 -> 28.6 ms, clumpy 512^3 disk (4e7) 519 -> 318 ms.
+template <typename R, int GK, bool LUT>
+__global__ void __launch_bounds__(kBlock) k_leg(const StageParams S) {
+  const unsigned long long count = *S.n_in;
+  if (count < S.min_n) return;
+  __shared__ StagePkg bufs[kWavesPerBlock][64];
+  __shared__ int lut[LUT ? kLutCells : 1];
+  const RunParams& P = S.P;
+  const GridDev& G = P.G;
+  LegMem<R, GK, LUT> M{static_cast<const R*>(P.rho)};
+  if constexpr (LUT) M.fill_lut(lut, G);
+  PkgFeed feed{bufs[threadIdx.x / 64]};
+  Leg<R> L;
+  L.ry.active = false;
+  L.mode = kLegPath;
+  double T = 0.0, tau_s = 0.0;
+  R kapR = R(0);
+  unsigned q = 0, slot = 0, lam = 0;
+  bool busy = false;
+  unsigned long long x_path = 0, x_loc = 0;
+  for (;;) {
+    if (busy && !L.ry.active) {
+      const StagePkg& p = S.in[q];
+      if (L.mode == kLegPath) {
+        T = (double)L.ry.tau;
+        if (T == 0.0) {  // nothing to interact with: the package leaves
+          S.leg[q] = StageLeg{0.0, 0.0};
+          busy = false;
+        } else {
+          tau_s = forced_depth(P, slot, lam, S.n, T);
+          L.tau_sR = (R)tau_s;
+          L.found = false;
+          L.mode = kLegLocate;
+          leg_restart<R, GK>(L, G, p.r, p.k);
+        }
+      } else if (L.found || L.mode == kLegLast) {  // the interaction point
+        double s = L.ry.tin + L.last;
+        if (L.found)
+          s = ray_cell_entry64<R, GK>(L.ry, G, p.r, p.k) +
+              (tau_s - (double)L.tau_prev) / (P.lam[lam].kappa * (double)L.rho_hit);
+        S.leg[q] = StageLeg{T, s};
+        busy = false;
+      } else {  // tau_s reached the total by rounding
+        L.mode = kLegLast;
+        L.tau_sR = R(INFINITY);
+        L.last = 0.0;
+        leg_restart<R, GK>(L, G, p.r, p.k);
+      }
+    }
+    bool want = !busy;
+    StagePkg p;
+    feed.take(S, count, want, p, q);
+    if (!busy && !want) {
+      busy = true;
+      slot = p.slot;
+      lam = p.lam;
+      kapR = (R)P.lam[lam].kappa;
+      L.mode = kLegPath;
+      L.found = false;
+      L.tau_sR = R(INFINITY);
+      L.comp = R(0);
+      ray_begin<R, GK>(L.ry, G, p.r, p.k);
+    }
+    const int n_busy = __popcll(__ballot(busy));
+    if (n_busy == 0) break;
+    for (;;) {
+      const int n_act = __popcll(__ballot(L.ry.active));
+      if (n_act == 0 || n_busy - n_act >= P.batch) break;
+      if (L.ry.active) {
+        const unsigned x = leg_step(L, G, kapR, M);
+        if (L.mode == kLegPath)
+          x_path += x;
+        else if (L.mode == kLegLocate)
+          x_loc += x;
+      }
+    }
+  }
+  const unsigned long long a0 = wave_sum_u64(x_path), a1 = wave_sum_u64(x_loc);
+  if (__lane_id() == 0) {
+    if (a0) atomicAdd(P.xstats + 0, a0);
+    if (a1) atomicAdd(P.xstats + 1, a1);
+  }
+}
+
+// Places for the jobs (n_jobs per thread) and the survivors (alive) of a
+// workgroup's iteration, in thread order: one atomic each per workgroup on the
+// queue's and the list's counters.  Called by every thread; `it` is the
+// iteration, the same in all of them (the LDS words alternate, so one
+// iteration's reads need no barrier against the next one's writes).
+struct StageSlots {
+  unsigned packed[2][kWavesPerBlock];
+  unsigned long long jobs[2], list[2];
+};
+
+__device__ __forceinline__ void stage_reserve(StageSlots& sh, int it, unsigned n_jobs, bool alive,
+                                              unsigned long long* job_ctr, unsigned long long* list_ctr,
+                                              unsigned long long& job_at, unsigned long long& list_at) {
+  const int lane = __lane_id(), wave = threadIdx.x / 64, b = it & 1;
+  const unsigned own = n_jobs | (alive ? 1u << 16 : 0u);  // 256 threads x 8 frames: no carry
+  unsigned v = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned u = __shfl_up(v, off);
+    if (lane >= off) v += u;
+  }
+  if (lane == 63) sh.packed[b][wave] = v;
+  __syncthreads();
+  unsigned before = v - own, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) {
+    const unsigned p = sh.packed[b][w];
+    if (w < wave) before += p;
+    total += p;
+  }
+  if (threadIdx.x == 0) {
+    sh.jobs[b] = (total & 0xffffu) ? atomicAdd(job_ctr, (unsigned long long)(total & 0xffffu)) : 0ull;
+    sh.list[b] = (total >> 16) ? atomicAdd(list_ctr, (unsigned long long)(total >> 16)) : 0ull;
+  }
+  __syncthreads();
+  job_at = sh.jobs[b] + (before & 0xffffu);
+  list_at = sh.list[b] + (before >> 16);
+}
+
+__device__ __forceinline__ void stage_put(const StageParams& S, unsigned long long at, unsigned slot, unsigned lam,
+                                          const double r[3], const double k[3], double W) {
+  S.out[at] = StagePkg{{r[0], r[1], r[2]}, {k[0], k[1], k[2]}, W, slot, lam};
+  S.keys[at] = stage_key(S.K, r);
+}
+
+__device__ __forceinline__ void stage_counts(const RunParams& P, const StageCounts& c) {
+  const double s_abs = wave_sum(c.s_abs), s_esc = wave_sum(c.s_esc), s_trunc = wave_sum(c.s_trunc);
+  const unsigned long long a2 = wave_sum_u64(c.x_peel), a3 = wave_sum_u64(c.n_ev), a4 = wave_sum_u64(c.n_pk),
+                           a5 = wave_sum_u64(c.n_pl), a6 = wave_sum_u64(c.n_dep);
+  if (__lane_id() != 0) return;
+  if (s_abs != 0.0) atomic_add_f64(P.dstats + 0, s_abs);
+  if (s_esc != 0.0) atomic_add_f64(P.dstats + 1, s_esc);
+  if (s_trunc != 0.0) atomic_add_f64(P.dstats + 2, s_trunc);
+  if (a2) atomicAdd(P.xstats + 2, a2);
+  if (a3) atomicAdd(P.xstats + 3, a3);
+  if (a4) atomicAdd(P.xstats + 4, a4);
+  if (a5) atomicAdd(P.xstats + 5, a5);
+  if (a6) atomicAdd(P.xstats + 6, a6);
+}
+
+template <typename R, int GK, bool INST, int PASS>
+__global__ void __launch_bounds__(kBlock) k_emit(const StageParams S) {
+  __shared__ StageSlots sh;
+  const RunParams& P = S.P;
+  LifeMem<R, GK, INST> M{static_cast<const R*>(P.rho), P, nullptr, nullptr, nullptr, nullptr, 0};
+  StageCounts c;
+  int it = 0;
+  for (unsigned long long base = blockIdx.x * (unsigned long long)kBlock; base < P.n_chunk;
+       base += (unsigned long long)gridDim.x * kBlock, ++it) {
+    const unsigned slot = (unsigned)(base + threadIdx.x);
+    unsigned lam = 0, mask = 0;
+    double r[3], k[3], W = 0.0;
+    const bool item = slot < P.n_chunk, alive = item && stage_emit(P, M, slot, lam, r, k, W);
+    c.n_pk += item;
+    if (alive) mask = stage_frames(P, M, 0, r);
+    unsigned long long job_at, list_at;
+    stage_reserve(sh, it, __popc(mask), alive, P.work + kJobCounter, S.n_out, job_at, list_at);
+    if (!alive) continue;
+    stage_peel<R, PASS>(P, M, 0, r, k, W, slot, lam, P.lam[lam], mask, job_at, c);
+    stage_put(S, list_at, slot, lam, r, k, W);
+  }
+  stage_counts(P, c);
+}
+
+template <typename R, int GK, bool INST, int PASS>
+__global__ void __launch_bounds__(kBlock) k_event(const StageParams S) {
+  __shared__ StageSlots sh;
+  const RunParams& P = S.P;
+  const unsigned long long count = *S.n_in;
+  if (count < S.min_n) return;
+  LifeMem<R, GK, INST> M{static_cast<const R*>(P.rho), P, nullptr, nullptr, nullptr, nullptr, 0};
+  StageCounts c;
+  int it = 0;
+  for (unsigned long long base = blockIdx.x * (unsigned long long)kBlock; base < count;
+       base += (unsigned long long)gridDim.x * kBlock, ++it) {
+    const unsigned long long q = base + threadIdx.x;
+    StagePkg p{{0.0, 0.0, 0.0}, {0.0, 0.0, 1.0}, 0.0, 0u, 0u};
+    unsigned mask = 0;
+    bool moved = false, alive = false;
+    if (q < count) {
+      p = S.in[q];
+      const StageLeg leg = S.leg[q];
+      const LamDev& O = P.lam[p.lam];
+      moved = stage_move<PASS>(P, M, O, p.slot, S.n, leg.T, leg.s, p.r, p.k, p.W, c);
+      if (moved) {
+        mask = stage_frames(P, M, S.n + 1, p.r);
+        alive = !stage_ends(P, O, S.n + 1, p.W);
+        if (!alive) c.s_trunc += p.W;
+      }
+    }
+    unsigned long long job_at, list_at;
+    stage_reserve(sh, it, __popc(mask), alive, P.work + kJobCounter, S.n_out, job_at, list_at);
+    if (!moved) continue;
+    const LamDev& O = P.lam[p.lam];
+    stage_peel<R, PASS>(P, M, S.n + 1, p.r, p.k, p.W, p.slot, p.lam, O, mask, job_at, c);
+    if (!alive) continue;
+    stage_turn(P, O, p.slot, p.lam, S.n, p.k);
+    stage_put(S, list_at, p.slot, p.lam, p.r, p.k, p.W);
+  }
+  stage_counts(P, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -518,8 +844,44 @@ __global__ void __launch_bounds__(kSortThreads) k_scatter(const unsigned* __rest
   }
 }
 
+// A list of packages in the order of their position keys: k_count counts
+// the keys of each of kSortBlocks parts of the list, and from the scanned
+// counts k_move writes every package to its sorted place.  Nothing is done
+// with a list shorter than min_n.
+constexpr int kStageKeyCount = 1 << kStageKeyBits;
+__global__ void __launch_bounds__(kSortThreads) k_count(const unsigned* __restrict__ keys,
+                                                        const unsigned long long* __restrict__ n_ptr,
+                                                        unsigned* __restrict__ counts, unsigned long long min_n) {
+  const unsigned long long n = *n_ptr;
+  if (n < min_n) return;
+  __shared__ unsigned h[kStageKeyCount];
+  for (int i = threadIdx.x; i < kStageKeyCount; i += kSortThreads) h[i] = 0u;
+  __syncthreads();
+  unsigned long long lo, hi;
+  sort_part(n, lo, hi);
+  for (unsigned long long j = lo + threadIdx.x; j < hi; j += kSortThreads) atomicAdd(h + keys[j], 1u);
+  __syncthreads();
+  for (int i = threadIdx.x; i < kStageKeyCount; i += kSortThreads) counts[(size_t)i * kSortBlocks + blockIdx.x] = h[i];
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_move(const StagePkg* __restrict__ src,
+                                                       const unsigned* __restrict__ keys,
+                                                       const unsigned long long* __restrict__ n_ptr,
+                                                       const unsigned* __restrict__ starts,
+                                                       StagePkg* __restrict__ dst, unsigned long long min_n) {
+  const unsigned long long n = *n_ptr;
+  if (n < min_n) return;
+  unsigned long long lo, hi;
+  sort_part(n, lo, hi);
+  __shared__ unsigned h[kStageKeyCount];
+  for (int i = threadIdx.x; i < kStageKeyCount; i += kSortThreads) h[i] = starts[(size_t)i * kSortBlocks + blockIdx.x];
+  __syncthreads();
+  for (unsigned long long j = lo + threadIdx.x; j < hi; j += kSortThreads) dst[atomicAdd(h + keys[j], 1u)] = src[j];
+}
+
 // Exclusive scan of counts[0, n) into starts[0, n] (the total in starts[n])
-// in three launches:
+// in three launches (which do nothing where the list that the counts are of,
+// *len long, is shorter than min_n; len null: always):
 // k_scan_tiles scans tiles of kScanTile counts within each block and writes
 // the tile totals, k_scan_top scans the totals in one block, k_scan_add adds
 // each tile's offset.
@@ -543,7 +905,9 @@ __device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* l
 
 __global__ void __launch_bounds__(kScanThreads) k_scan_tiles(const unsigned* __restrict__ counts,
                                                              unsigned* __restrict__ starts, unsigned* __restrict__ tiles,
-                                                             long long n) {
+                                                             long long n, const unsigned long long* __restrict__ len,
+    unsigned long long min_n) {
+  if (len && *len < min_n) return;
   __shared__ unsigned lds[kScanThreads];
   const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanPer;
   unsigned v[kScanPer], s = 0;
@@ -563,7 +927,9 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_tiles(const unsigned* __r
 }
 
 __global__ void __launch_bounds__(kTopThreads) k_scan_top(unsigned* __restrict__ tiles, long long n_tiles,
-                                                          unsigned* __restrict__ starts, long long n) {
+                                                          unsigned* __restrict__ starts, long long n, const unsigned long long* __restrict__ len,
+    unsigned long long min_n) {
+  if (len && *len < min_n) return;
   __shared__ unsigned lds[kTopThreads];
   const long long per = (n_tiles + kTopThreads - 1) / kTopThreads;
   const long long lo = threadIdx.x * per, hi = lo + per < n_tiles ? lo + per : n_tiles;
@@ -580,7 +946,9 @@ __global__ void __launch_bounds__(kTopThreads) k_scan_top(unsigned* __restrict__
 }
 
 __global__ void __launch_bounds__(kScanThreads) k_scan_add(unsigned* __restrict__ starts,
-                                                           const unsigned* __restrict__ tiles, long long n) {
+                                                           const unsigned* __restrict__ tiles, long long n, const unsigned long long* __restrict__ len,
+    unsigned long long min_n) {
+  if (len && *len < min_n) return;
   const long long base = (long long)blockIdx.x * kScanTile;
   const unsigned off = tiles[blockIdx.x];
   for (int i = threadIdx.x; i < kScanTile; i += kScanThreads)
@@ -1460,9 +1828,11 @@ int run_peel_jobs(const PeelQueue& q, const RunParams& P, unsigned long long* ct
                      q.counts);
   const long long n_tiles = (n_cnt + kScanTile - 1) / kScanTile;
   hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)n_tiles), dim3(kScanThreads), 0, st, q.counts, q.starts, q.tiles,
-                     n_cnt);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kTopThreads), 0, st, q.tiles, n_tiles, q.starts, n_cnt);
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)n_tiles), dim3(kScanThreads), 0, st, q.starts, q.tiles, n_cnt);
+                     n_cnt, nullptr, 0ull);
+  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kTopThreads), 0, st, q.tiles, n_tiles, q.starts, n_cnt,
+                     nullptr, 0ull);
+  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)n_tiles), dim3(kScanThreads), 0, st, q.starts, q.tiles, n_cnt,
+                     nullptr, 0ull);
   hipLaunchKernelGGL(k_hot, dim3((unsigned)((q.n_keys + 32 * kSortThreads - 1) / (32 * kSortThreads))),
                      dim3(kSortThreads), 0, st, q.starts, (int)q.n_keys, q.hot);
   hipLaunchKernelGGL(k_scatter, dim3(kSortBlocks), dim3(kSortThreads), 0, st, q.keys, ctr, q.cap, (int)q.n_keys,
@@ -1596,6 +1966,124 @@ int launch_life(const RunParams& P, bool inst, int nblk, hipStream_t st) {
 constexpr int kEventsKept = 32;
 constexpr size_t kScratchBytes = size_t(1) << 34, kQueueBytes = size_t(1) << 35;
 
+// Smallest list of packages that is worth a stage of its own, smallest chunk
+// that runs in stages, and the most orders in stages (seven launches each;
+// what is left after them the lane machine runs).  A stage lasts at least as
+// long as its longest walk, 0.1-0.5 ms, however short its list, and the lane
+// machine overlaps those walks with other packages' events: with the stages
+// going on to lists of 2^16 / 2^18 / 2^20 packages, forward runs of 1e6
+// packages take 8.8 / 8.2 / 6.8 ms on a 32^3 grid (lane machine alone 6.8),
+// 9.8 / 9.3 / 9.6 on the spiral (9.8), 18.1 / 17.1 / 17.9 on a k-d tree (18.2);
+// 4e6 packages 15.1 / 24.3 / 46.8 ms at 2^20 (lane machine alone 17.0 / 32.6 /
+// 60.0), 1e7 packages 32.8 / 54.6 / 106 ms (41.5 / 81.1 / 146).
+constexpr unsigned long long kStageMin = 1ull << 20, kStageItems = 1ull << 20;
+constexpr int kStageOrders = 12;
+// Lanes of a wavefront that wait before k_leg serves them: a pass over the
+// waiting lanes costs as much as some ten blocks of crossings.  Clumpy 512^3
+// disk (4e7 packages): all stages 367 / 349 / 320 ms at 24 / 32 / 48; spiral
+// 31.7 / 31.0 / 31.6 ms.
+constexpr int kBatchLeg = 48;
+// Budget of the package lists (at most an eighth of the free memory).
+constexpr size_t kStageBytes = size_t(1) << 33;
+
+// Device memory of a chunk of `n` packages in stages: the list and the
+// ordered list, the keys, the legs' results, the count matrix and its scan,
+// and the counters of every order (its list's length, its slices' next
+// packages).
+struct StageBytes {
+  size_t pkg, keys, leg, counts, tiles, counters;
+  explicit StageBytes(unsigned long long n)
+      : pkg(align256(sizeof(StagePkg) * n)),
+        keys(align256(sizeof(unsigned) * n)),
+        leg(align256(sizeof(StageLeg) * n)),
+        counts(align256(sizeof(unsigned) * ((size_t)kStageKeyCount * kSortBlocks + 1))),
+        tiles(align256(sizeof(unsigned) * ((size_t)kStageKeyCount * kSortBlocks / kScanTile + 1))),
+        counters(align256(sizeof(unsigned long long) * (1 + kXcds) * (kStageOrders + 1))) {}
+  size_t total() const { return 2 * pkg + keys + leg + 2 * counts + tiles + counters; }
+};
+constexpr size_t kStagePerPackage = 2 * sizeof(StagePkg) + sizeof(unsigned) + sizeof(StageLeg);
+
+template <typename R, int GK, bool INST, int PASS>
+int run_stages_k(StageParams S, unsigned long long cap, unsigned char* mem, int orders, int blocks_per_cu, int batch,
+                 hipStream_t st) {
+  const StageBytes by(cap);
+  StagePkg* const list = reinterpret_cast<StagePkg*>(mem);
+  StagePkg* const sorted = reinterpret_cast<StagePkg*>(mem += by.pkg);
+  S.keys = reinterpret_cast<unsigned*>(mem += by.pkg);
+  S.leg = reinterpret_cast<StageLeg*>(mem += by.keys);
+  unsigned* const counts = reinterpret_cast<unsigned*>(mem += by.leg);
+  unsigned* const starts = reinterpret_cast<unsigned*>(mem += by.counts);
+  unsigned* const tiles = reinterpret_cast<unsigned*>(mem += by.counts);
+  unsigned long long* const ctr = reinterpret_cast<unsigned long long*>(mem += by.tiles);
+  const RunParams P = S.P;  // with the lane machine's event batch
+  S.P.batch = batch > 0 ? batch : kBatchLeg;
+  S.K = stage_keys(S.P.G);
+  S.in = sorted;
+  S.out = list;
+  S.min_n = kStageMin;
+  if (int e = zero_fill(reinterpret_cast<double*>(ctr), (1 + kXcds) * (kStageOrders + 1), st)) return e;
+  constexpr bool CAN = GK == kGridRegular;  // may use the address table
+  void (*leg)(StageParams) = CAN && lut_cells(S.P.G) <= kLutCells ? k_leg<R, GK, CAN> : k_leg<R, GK, false>;
+  constexpr auto tail = k_tail<R, PASS != kPassForward, GK, INST>;
+  int n_emit = 0, n_leg = 0, n_event = 0, n_tail = 0;
+  if (int e = persistent_grid(k_emit<R, GK, INST, PASS>, 0, &n_emit)) return e;
+  if (int e = persistent_grid(leg, blocks_per_cu, &n_leg)) return e;
+  if (int e = persistent_grid(k_event<R, GK, INST, PASS>, 0, &n_event)) return e;
+  if (int e = persistent_grid(tail, blocks_per_cu, &n_tail)) return e;
+  S.n = 0;
+  S.n_out = ctr;
+  hipLaunchKernelGGL((k_emit<R, GK, INST, PASS>), dim3(n_emit), dim3(kBlock), 0, st, S);
+  const long long n_cnt = (long long)kStageKeyCount * kSortBlocks, n_tiles = (n_cnt + kScanTile - 1) / kScanTile;
+  for (int n = 0; n < orders; ++n) {
+    S.n = n;
+    S.n_in = ctr + n;
+    S.n_out = ctr + n + 1;
+    S.next = ctr + kStageOrders + 1 + kXcds * n;
+    hipLaunchKernelGGL(k_count, dim3(kSortBlocks), dim3(kSortThreads), 0, st, S.keys, S.n_in, counts, S.min_n);
+    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)n_tiles), dim3(kScanThreads), 0, st, counts, starts, tiles, n_cnt,
+                       S.n_in, S.min_n);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kTopThreads), 0, st, tiles, n_tiles, starts, n_cnt, S.n_in, S.min_n);
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)n_tiles), dim3(kScanThreads), 0, st, starts, tiles, n_cnt, S.n_in,
+                       S.min_n);
+    hipLaunchKernelGGL(k_move, dim3(kSortBlocks), dim3(kSortThreads), 0, st, list, S.keys, S.n_in, starts, sorted,
+                       S.min_n);
+    hipLaunchKernelGGL(leg, dim3(n_leg), dim3(kBlock), 0, st, S);
+    hipLaunchKernelGGL((k_event<R, GK, INST, PASS>), dim3(n_event), dim3(kBlock), 0, st, S);
+  }
+  hipLaunchKernelGGL(tail, dim3(n_tail), dim3(kBlock), 0, st, P, StageTail{list, ctr, S.min_n, orders + 1});
+  HIPCHK(hipGetLastError());
+  return 0;
+}
+
+template <typename R, bool INST>
+int run_stages_c(const StageParams& S, int pass, unsigned long long cap, unsigned char* mem, int orders, int bpc,
+                 int batch, hipStream_t st) {
+  auto go = [&](auto gk) -> int {
+    constexpr int GK = decltype(gk)::value;
+    return pass == kPassForward ? run_stages_k<R, GK, INST, kPassForward>(S, cap, mem, orders, bpc, batch, st)
+                                : run_stages_k<R, GK, INST, kPassA>(S, cap, mem, orders, bpc, batch, st);
+  };
+  switch (S.P.G.kind) {
+    case kGridRect: return go(std::integral_constant<int, kGridRect>{});
+    case kGridTree: return go(std::integral_constant<int, kGridTree>{});
+    default: return go(std::integral_constant<int, kGridRegular>{});
+  }
+}
+
+// One chunk's life cycle in stages: the forward run, or the adjoint's pass
+// A, over memory of StageBytes(cap) bytes.
+int run_stages(const RunParams& P, bool f32, bool inst, int pass, unsigned long long cap, unsigned char* mem,
+               int orders, int blocks_per_cu, int batch, hipStream_t st) {
+  StageParams S;
+  std::memset(&S, 0, sizeof S);
+  S.P = P;
+  if (f32)
+    return inst ? run_stages_c<float, true>(S, pass, cap, mem, orders, blocks_per_cu, batch, st)
+                : run_stages_c<float, false>(S, pass, cap, mem, orders, blocks_per_cu, batch, st);
+  return inst ? run_stages_c<double, true>(S, pass, cap, mem, orders, blocks_per_cu, batch, st)
+              : run_stages_c<double, false>(S, pass, cap, mem, orders, blocks_per_cu, batch, st);
+}
+
 // Shared driver of run_photons and backward_density.
 int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_optics* optics, int n_src,
          const mcrt_source* sources, int n_det, const mcrt_detector* detectors, const mcrt_opts* opts,
@@ -1687,6 +2175,17 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
         most, std::max<size_t>(1 << 16, std::min(kQueueBytes, free_b / 4) /
                                             ((size_t)n_det * 8 * kQueueBytesPerRay)));
   if (opts->max_chunk > 0) most = std::min<unsigned long long>(most, (unsigned long long)opts->max_chunk);
+  // in stages (mcrt_stage.hpp): runs without an absorbed tally, and pass A of
+  // the image loss's density gradient, in chunks with enough packages to fill
+  // the card order after order
+  const int orders = (int)std::min<long long>(kStageOrders, host::tape_events(*optics, *opts) - 1);
+  bool staged = !att && !optg && !(adjoint && adj_abs_dev) && !tape_adj && !P.absorbed && opts->peel_queue != -1 &&
+                std::min<unsigned long long>(most, P.n_items) >= kStageItems;
+  if (staged) {
+    const unsigned long long fit = std::min(kStageBytes, free_b / 8) / kStagePerPackage;
+    staged = fit >= kStageItems;
+    if (staged) most = std::min(most, fit);
+  }
   const unsigned long long n_chunks = (P.n_items + most - 1) / most;
   const unsigned long long chunk = (P.n_items + n_chunks - 1) / n_chunks;
   // the adjoint's event scratch, then (optics gradients) the pass-B sums
@@ -1712,7 +2211,8 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
   const size_t off_lums = off_ctot + (cells ? align256(sizeof(double) * nl + 8) : 0);
   const size_t off_aab = off_lums + (optg ? align256(sizeof(double) * pr.lums.size()) : 0);
   const bool aabs = adjoint && adj_abs_dev;  // a loss on the absorbed tally: its adjoint, bricked
-  const size_t bytes = off_aab + (aabs ? align256(sizeof(double) * (size_t)nl * P.G.ncell_pad) : 0);
+  const size_t off_stg = off_aab + (aabs ? align256(sizeof(double) * (size_t)nl * P.G.ncell_pad) : 0);
+  const size_t bytes = off_stg + (staged ? StageBytes(chunk).total() : 0);
 
   DeviceBlock blk;
   blk.st = st;
@@ -1808,8 +2308,11 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
   };
   auto life_launch = [&](bool adj) -> int {
     if (int e = sp.mark(kSpanLife, st)) return e;
-    const int r = adj ? (f32 ? launch_life<float, true>(P, full, nblk, st) : launch_life<double, true>(P, full, nblk, st))
-                      : (f32 ? launch_life<float, false>(P, full, nblk, st)
+    const int r = staged && !(adj && P.split == 2)
+                      ? run_stages(P, f32, inst, adj ? kPassA : kPassForward, chunk, blk.ptr + off_stg, orders,
+                                   opts->launch_blocks, opts->event_batch, st)
+                  : adj  ? (f32 ? launch_life<float, true>(P, full, nblk, st) : launch_life<double, true>(P, full, nblk, st))
+                         : (f32 ? launch_life<float, false>(P, full, nblk, st)
                              : launch_life<double, false>(P, full, nblk, st));
     if (r) return r;
     ++launches;

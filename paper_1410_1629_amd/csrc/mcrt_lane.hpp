@@ -89,6 +89,12 @@ struct PeelJob {
   unsigned char d;
 };
 
+// A package between two of its events, as the staged kernels keep it
+// (mcrt_stage.hpp): one 64-byte record.
+struct alignas(64) StagePkg {
+  double r[3], k[3], W;
+  unsigned slot, lam;  // index in the chunk, wavelength
+};
 // Depth bits the adjoint's queued rays drop (RunParams::depth_drop).
 // Measured with the tape (spiral, 1e7 packages): deposit walks 23.6 ms with 4
 // depth bits, 26.0 with 6 and 26.0 with none; the forward's peel walks on
@@ -277,6 +283,39 @@ MCRT_HD void keep_q(Lane<R>& L, const RunParams& P, Mem& M, double q) {
     M.ev_store(L.slot, L.n, 1 + L.det, q);
   else
     M.ev_add_beyond(L.slot, q);
+}
+
+// Whether an accessor's fetch() numbers packages that are already on their
+// way (Mem::kResume): M.resume_count() of them, package i in M.resume_pkg(i),
+// each with M.resume_events() events behind its emission.
+template <class M, class = void>
+struct Resumes : std::false_type {};
+template <class M>
+struct Resumes<M, std::void_t<decltype(M::kResume)>> : std::bool_constant<M::kResume> {};
+
+// Takes over package p after its event n: its next leg starts.
+template <typename R>
+MCRT_HD void lane_resume(Lane<R>& L, const RunParams& P, const LamDev& O, const StagePkg& p, int n) {
+  L.slot = (int)p.slot;
+  L.lam = (int)p.lam;
+  L.pkg = P.first + (P.item0 + p.slot - (unsigned long long)p.lam * P.n_pkg);
+  L.lam_cell = (long long)L.lam * P.G.ntal;
+  L.kap = O.kappa;
+  L.kapR = (R)L.kap;
+  L.alb = O.albedo;
+  L.g = O.g;
+  L.w0 = O.w0;
+  L.pass = 0;
+  L.Gacc = L.Gabs = L.Ge = 0.0;
+  for (int a = 0; a < 3; ++a) {
+    L.r[a] = p.r[a];
+    L.k[a] = p.k[a];
+  }
+  L.W = p.W;
+  L.n = n;
+  L.is_emit = n == 0;
+  L.det = 0;
+  L.phase = PH_PATH_START;
 }
 
 // Runs the lane's events until its next walk is set up (ry.active) or no
@@ -510,6 +549,15 @@ MCRT_HD void lane_events(Lane<R>& L, const RunParams& P, Mem& M) {
         L.x_path = L.x_loc = L.x_peel = L.n_dep = 0;
       }
       const unsigned long long k = M.fetch();
+      if constexpr (Resumes<Mem>::value) {
+        if (k >= M.resume_count()) {
+          L.done = true;
+        } else {
+          const StagePkg& p = M.resume_pkg(k);
+          lane_resume(L, P, M.lam((int)p.lam), p, M.resume_events());
+        }
+        continue;
+      }
       if (k >= P.n_chunk) {
         L.done = true;
       } else {
