@@ -49,13 +49,19 @@
  *    default stream) unless it returns statistics, in which case it waits
  *    for its own work to finish before returning.
  *  - Ownership: the caller owns every buffer; host structs and arrays are
- *    read only during the call.  The library keeps no state between calls.
- *    Each call allocates stream-ordered device memory (hipMallocAsync) for
- *    its tables, a bricked copy of the densities and, where it has one, a
- *    tally in the library's own cell order (the forward's absorbed tally
- *    takes up to twice the cells of the grid per wavelength: its cell units
- *    are padded to a power of two), the adjoint's event scratch and the
- *    peel-ray queue, and frees it on the stream when its work ends.
+ *    read only during the call.  No result, table or input is kept between
+ *    calls.  Each call works in stream-ordered device memory
+ *    (hipMallocAsync) for its tables, a bricked copy of the densities and,
+ *    where it has one, a tally in the library's own cell order (the
+ *    forward's absorbed tally takes up to twice the cells of the grid per
+ *    wavelength: its cell units are padded to a power of two), the
+ *    adjoint's event scratch, the peel-ray queue and the lists of a run in
+ *    stages.  The library keeps such blocks for later calls, at most 64 GiB
+ *    and a quarter of a device's memory, and gives them back when they go
+ *    unused, when less than half of the memory is free, or on
+ *    mcrt_release_workspaces.  Calls may run on several streams and threads:
+ *    a block serves one call at a time.  Under stream capture blocks are
+ *    neither kept nor reused.
  *  - Errors: 0 on success; MCRT_EINVAL for invalid arguments (nothing is
  *    launched), MCRT_EOVERFLOW when a segment buffer was too small,
  *    MCRT_EHIP for a HIP runtime error.  mcrt_last_error() returns a message
@@ -486,6 +492,10 @@ int backward(const mcrt_grid *grid, const void *rho_dev, const mcrt_optics *opti
 int dust_emission(const mcrt_grid *grid, const void *rho_dev, int precision, int n_abs, const double *absorbed_dev,
                   int n_lambda, const double *lambda, const double *dlambda, const double *kappa_abs,
                   double emissivity, double *temperature_dev, double *emission_dev, void *hip_stream);
+
+/* Gives the device memory that the library keeps between calls back (on
+ * every device; waits for the calls that used it).  Returns 0 or MCRT_EHIP. */
+int mcrt_release_workspaces(void);
 
 /* Message for the last nonzero return on the calling thread ("" if none). */
 const char *mcrt_last_error(void);

@@ -91,7 +91,7 @@ _lib = None
 # Exported symbols of include/mcrt.h.
 ABI_VERSION = 18  # MCRT_ABI_VERSION of the header these structs follow
 SYMBOLS = ("run_photons", "trace_path", "trace_path_noalloc", "peel_off", "backward_density", "backward",
-           "dust_emission", "mcrt_tape_bytes", "mcrt_last_error", "mcrt_abi_version")
+           "dust_emission", "mcrt_release_workspaces", "mcrt_tape_bytes", "mcrt_last_error", "mcrt_abi_version")
 NOALLOC_SCRATCH_BYTES = 96 << 20  # MCRT_NOALLOC_SCRATCH_BYTES
 
 
@@ -128,6 +128,8 @@ def load():
     lib.dust_emission.argtypes = [C.POINTER(Grid), P, C.c_int, C.c_int, P, C.c_int, C.POINTER(C.c_double),
                                   C.POINTER(C.c_double), C.POINTER(C.c_double), d, P, P, P]
     lib.dust_emission.restype = C.c_int
+    lib.mcrt_release_workspaces.argtypes = []
+    lib.mcrt_release_workspaces.restype = C.c_int
     lib.mcrt_last_error.argtypes = []
     lib.mcrt_last_error.restype = C.c_char_p
     lib.mcrt_tape_bytes.argtypes = [C.POINTER(Optics), C.c_int, C.POINTER(Opts)]
@@ -171,6 +173,12 @@ def probe(kind, buf, n_ops, reps=3, stream=None):
 def _check(rc):
     if rc != OK:
         raise McrtError(rc, load().mcrt_last_error().decode())
+
+
+def release_workspaces():
+    """mcrt_release_workspaces: gives back the device memory that the library
+    keeps between calls."""
+    _check(load().mcrt_release_workspaces())
 
 
 def _ptr(t):

@@ -1666,14 +1666,191 @@ int cell_cdf(const double* cell_lum, int nl, int ncell, double* cum, double* til
   return 0;
 }
 
-// Per-call device memory (problem tables, zeroed counters, the bricked
-// densities and tally): one allocation, ordered on the stream, released on
-// the stream when the call returns.
+// Per-call device memory (problem tables, counters, the bricked densities,
+// tallies, queues), ordered on the call's stream.  Blocks are kept between
+// calls: mapping and unmapping them took longer than the kernels (a 1e7
+// package step on the spiral needs 25 GB in four blocks, 176 ms of kernels and
+// up to 960 ms of mapping each time the stream was waited for in between).
+//
+// A kept block is idle memory of one device with an event of its last use.
+// A call takes one that is large enough (and not more than four times as
+// large) if that use is over or was on the same stream handle -- it waits for
+// the event on its stream either way -- so streams that overlapped still do,
+// each with blocks of its own.  Under stream capture nothing is kept or
+// taken.  Kept blocks are bounded (kKeepBytes, a quarter of the device,
+// kKeepBlocks) and go back on the stream that replaces them, when 32 calls
+// have not used them, as soon as less than half of the device's memory is
+// free, when an allocation fails, and with mcrt_release_workspaces.
+constexpr size_t kKeepBytes = size_t(64) << 30, kKeepLarge = size_t(256) << 20;
+constexpr size_t kKeepBlocks = 16;
+constexpr unsigned long long kKeepCalls = 32;
+
+struct Block {
+  unsigned char* ptr;
+  size_t bytes;
+  int dev;
+  hipStream_t st;    // of the last use
+  hipEvent_t done;   // end of the last use
+  unsigned long long use;
+};
+
+class BlockStore {
+ public:
+  // A block of at least `bytes` from the kept ones; false: none fits.
+  bool take(size_t bytes, int dev, hipStream_t st, Block& out) {
+    std::lock_guard<std::mutex> lock(mu_);
+    ++clock_;
+    size_t best = idle_.size();
+    for (size_t i = 0; i < idle_.size(); ++i) {
+      const Block& b = idle_[i];
+      if (b.dev != dev || b.bytes < bytes || b.bytes / 4 > std::max(bytes, size_t(16) << 20)) continue;
+      if (b.st != st && hipEventQuery(b.done) != hipSuccess) {
+        (void)hipGetLastError();
+        continue;
+      }
+      if (best == idle_.size() || b.bytes < idle_[best].bytes) best = i;
+    }
+    if (best == idle_.size()) return false;
+    out = idle_[best];
+    idle_.erase(idle_.begin() + (long)best);
+    return true;
+  }
+  // Keeps a block (its event recorded), and returns those that have to go.
+  void keep(Block b, size_t budget, std::vector<Block>& out) {
+    std::lock_guard<std::mutex> lock(mu_);
+    b.use = clock_;
+    idle_.push_back(b);
+    for (;;) {  // the longest unused first
+      size_t total = 0, old = idle_.size();
+      for (size_t i = 0; i < idle_.size(); ++i) {
+        if (idle_[i].dev != b.dev) continue;
+        total += idle_[i].bytes;
+        if (old == idle_.size() || idle_[i].use < idle_[old].use) old = i;
+      }
+      if (old == idle_.size() ||
+          (total <= budget && idle_.size() <= kKeepBlocks && idle_[old].use + kKeepCalls >= clock_))
+        return;
+      out.push_back(idle_[old]);
+      idle_.erase(idle_.begin() + (long)old);
+    }
+  }
+  // Removes the idle blocks of a device (dev < 0: of all), smaller ones than
+  // `below` only.
+  void drop(int dev, size_t below, std::vector<Block>& out) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (size_t i = idle_.size(); i-- > 0;)
+      if ((dev < 0 || idle_[i].dev == dev) && idle_[i].bytes < below) {
+        out.push_back(idle_[i]);
+        idle_.erase(idle_.begin() + (long)i);
+      }
+  }
+  size_t idle_bytes(int dev) {
+    std::lock_guard<std::mutex> lock(mu_);
+    size_t n = 0;
+    for (const Block& b : idle_)
+      if (b.dev == dev) n += b.bytes;
+    return n;
+  }
+
+ private:
+  std::mutex mu_;
+  std::vector<Block> idle_;
+  unsigned long long clock_ = 0;
+};
+
+BlockStore& block_store() {
+  static BlockStore* const s = new BlockStore;  // not destroyed: the runtime may be gone by then
+  return *s;
+}
+
+// Frees blocks on a stream of the current device, after their last use.
+void free_blocks(std::vector<Block>& blocks, hipStream_t st) {
+  for (Block& b : blocks) {
+    (void)hipStreamWaitEvent(st, b.done, 0);
+    (void)hipFreeAsync(b.ptr, st);
+    (void)hipEventDestroy(b.done);
+  }
+  blocks.clear();
+}
+
+bool stream_capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return c != hipStreamCaptureStatusNone;
+}
+
+// The device's free memory, counting the idle blocks (a call may take them
+// or give them back).
+int free_memory(size_t* free_b) {
+  size_t total_b = 0;
+  int dev = 0;
+  HIPCHK(hipMemGetInfo(free_b, &total_b));
+  HIPCHK(hipGetDevice(&dev));
+  *free_b += block_store().idle_bytes(dev);
+  return 0;
+}
+
 struct DeviceBlock {
   unsigned char* ptr = nullptr;
   hipStream_t st = nullptr;
+  Block b{};          // kept after the call (b.done set), else freed with it
+  int alloc(size_t bytes) {
+    int dev = 0;
+    HIPCHK(hipGetDevice(&dev));
+    const bool keep = !stream_capturing(st);
+    if (keep) {
+      if (block_store().take(bytes, dev, st, b)) {
+        ptr = b.ptr;
+        HIPCHK(hipStreamWaitEvent(st, b.done, 0));
+        return 0;
+      }
+      const size_t unit = bytes >= kKeepLarge ? size_t(64) << 20 : size_t(1) << 16;  // sizes that vary a little fit
+      bytes = (bytes + unit - 1) / unit * unit;
+    }
+    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&ptr), bytes, st);
+    if (e != hipSuccess && keep) {  // give the idle blocks back and try again
+      (void)hipGetLastError();
+      std::vector<Block> idle;
+      block_store().drop(dev, SIZE_MAX, idle);
+      if (!idle.empty()) {
+        free_blocks(idle, st);
+        HIPCHK(hipStreamSynchronize(st));
+        e = hipMallocAsync(reinterpret_cast<void**>(&ptr), bytes, st);
+      }
+    }
+    if (e != hipSuccess) {
+      ptr = nullptr;
+      return fail(MCRT_EHIP, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
+    }
+    if (keep && hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess) {
+      b.ptr = ptr;
+      b.bytes = bytes;
+      b.dev = dev;
+    }
+    return 0;
+  }
   ~DeviceBlock() {
-    if (ptr) (void)hipFreeAsync(ptr, st);
+    if (!ptr) return;
+    if (!b.done) {
+      (void)hipFreeAsync(ptr, st);
+      return;
+    }
+    std::vector<Block> gone;
+    size_t free_b = 0, total_b = 0;
+    b.st = st;
+    if (hipEventRecord(b.done, st) != hipSuccess) {
+      (void)hipFreeAsync(ptr, st);
+      (void)hipEventDestroy(b.done);
+      return;
+    }
+    size_t budget = kKeepBytes;
+    if (b.bytes >= kKeepLarge && hipMemGetInfo(&free_b, &total_b) == hipSuccess)
+      budget = free_b < total_b / 2 ? 0 : std::min(budget, total_b / 4);
+    block_store().keep(b, budget, gone);
+    free_blocks(gone, st);
   }
 };
 
@@ -1722,8 +1899,7 @@ struct Spans {
 // matrix (keys x kSortBlocks), its scan and the scan's tile totals.
 constexpr size_t kQueueBytesPerRay = sizeof(PeelJob) + 3 * sizeof(unsigned) + sizeof(unsigned short);
 struct PeelQueue {
-  unsigned char* ptr = nullptr;
-  hipStream_t st = nullptr;
+  DeviceBlock mem;
   unsigned long long cap = 0;
   long long n_keys = 0;
   int n_sub = 0;  // counters of k_refine: 2^(width of the second keys)
@@ -1731,9 +1907,6 @@ struct PeelQueue {
   unsigned *keys = nullptr, *perm = nullptr, *idx = nullptr, *counts = nullptr, *starts = nullptr, *tiles = nullptr;
   unsigned* hot = nullptr;  // bit k: key k's run is at least kHotRun rays (not refined)
   unsigned short* subs = nullptr;
-  ~PeelQueue() {
-    if (ptr) (void)hipFreeAsync(ptr, st);
-  }
 };
 
 // Capacity per chunk of `chunk` packages: mcrt_opts.peel_queue, or by
@@ -1744,7 +1917,7 @@ struct PeelQueue {
 // rays per package and frame.
 int make_peel_queue(const mcrt_opts& o, const host::Prepared& pr, unsigned long long chunk, hipStream_t st,
                     PeelQueue& q) {
-  q.st = st;
+  q.mem.st = st;
   q.n_keys = pr.n_keys;
   q.n_sub = 1 << pr.sub_bits;
   if (q.n_sub > kSubKeys) return fail(MCRT_EINVAL, "second sort keys of %d bits exceed the sort's counters", pr.sub_bits);
@@ -1754,8 +1927,8 @@ int make_peel_queue(const mcrt_opts& o, const host::Prepared& pr, unsigned long 
   } else {
     cap = chunk * (unsigned long long)pr.P.n_det * 8ull;
     cap = std::min(std::max(cap, 1ull << 16), 1ull << 31);
-    size_t free_b = 0, total_b = 0;
-    HIPCHK(hipMemGetInfo(&free_b, &total_b));
+    size_t free_b = 0;
+    if (int e = free_memory(&free_b)) return e;
     cap = std::min<unsigned long long>(cap, free_b / 4 / kQueueBytesPerRay);
     if (cap == 0) return 0;
   }
@@ -1769,17 +1942,18 @@ int make_peel_queue(const mcrt_opts& o, const host::Prepared& pr, unsigned long 
   const size_t off_tiles = off_start + align256(sizeof(unsigned) * (n_cnt + 1));
   const size_t off_hot = off_tiles + align256(sizeof(unsigned) * (n_cnt / kScanTile + 1));
   const size_t bytes = off_hot + align256(sizeof(unsigned) * (host::kSortKeys / 32));
-  HIPCHK(hipMallocAsync(reinterpret_cast<void**>(&q.ptr), bytes, st));
+  if (int e = q.mem.alloc(bytes)) return e;
+  unsigned char* const ptr = q.mem.ptr;
   q.cap = cap;
-  q.jobs = reinterpret_cast<PeelJob*>(q.ptr);
-  q.keys = reinterpret_cast<unsigned*>(q.ptr + off_keys);
-  q.perm = reinterpret_cast<unsigned*>(q.ptr + off_perm);
-  q.idx = reinterpret_cast<unsigned*>(q.ptr + off_idx);
-  q.subs = reinterpret_cast<unsigned short*>(q.ptr + off_subs);
-  q.counts = reinterpret_cast<unsigned*>(q.ptr + off_cnt);
-  q.starts = reinterpret_cast<unsigned*>(q.ptr + off_start);
-  q.tiles = reinterpret_cast<unsigned*>(q.ptr + off_tiles);
-  q.hot = reinterpret_cast<unsigned*>(q.ptr + off_hot);
+  q.jobs = reinterpret_cast<PeelJob*>(ptr);
+  q.keys = reinterpret_cast<unsigned*>(ptr + off_keys);
+  q.perm = reinterpret_cast<unsigned*>(ptr + off_perm);
+  q.idx = reinterpret_cast<unsigned*>(ptr + off_idx);
+  q.subs = reinterpret_cast<unsigned short*>(ptr + off_subs);
+  q.counts = reinterpret_cast<unsigned*>(ptr + off_cnt);
+  q.starts = reinterpret_cast<unsigned*>(ptr + off_start);
+  q.tiles = reinterpret_cast<unsigned*>(ptr + off_tiles);
+  q.hot = reinterpret_cast<unsigned*>(ptr + off_hot);
   return 0;
 }
 
@@ -2165,8 +2339,8 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
   const size_t per_item = sizeof(double) * ((size_t)ev_max * ev_k + (att ? 0 : 1 + (optg ? 4 : 0)));
   const bool queued = peel && opts->peel_queue != -1;  // the attached gradient queues its deposit walks only
   P.depth_drop = adjoint ? kDepthDropAdjoint : 0;
-  size_t free_b = 0, total_b = 0;
-  HIPCHK(hipMemGetInfo(&free_b, &total_b));
+  size_t free_b = 0;
+  if (int e = free_memory(&free_b)) return e;
   unsigned long long most = P.n_items;
   if (adjoint)
     most = std::min<unsigned long long>(most, std::max<size_t>(1 << 16, std::min(kScratchBytes, free_b / 4) / per_item));
@@ -2216,7 +2390,7 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
 
   DeviceBlock blk;
   blk.st = st;
-  HIPCHK(hipMallocAsync(reinterpret_cast<void**>(&blk.ptr), bytes, st));
+  if (int e = blk.alloc(bytes)) return e;
   if (cells) {
     double* cum = reinterpret_cast<double*>(blk.ptr + off_cum);
     if (int e = cell_cdf(static_cast<const double*>(sources[pr.cell_src].cell_lum), nl, P.G.ncell, cum,
@@ -2513,7 +2687,7 @@ int trace_impl(const mcrt_grid* grid, const void* rho_dev, double kappa, int pre
   if (fixed) {
     if (int e = scratch_address(&base)) return e;
   } else {
-    HIPCHK(hipMallocAsync(reinterpret_cast<void**>(&blk.ptr), bytes, st));
+    if (int e = blk.alloc(bytes)) return e;
     base = blk.ptr;
   }
   if (tables || !fixed) {
@@ -2555,6 +2729,29 @@ uint64_t mcrt_tape_bytes(const mcrt_optics* optics, int n_det, const mcrt_opts* 
     return mcrt::host::tape_bytes(optics, n_det, opts);
   } catch (...) {
     return 0;
+  }
+}
+
+int mcrt_release_workspaces(void) {
+  try {
+    mcrt::host::last_error().clear();
+    std::vector<Block> idle;
+    block_store().drop(-1, SIZE_MAX, idle);
+    int dev = 0;
+    HIPCHK(hipGetDevice(&dev));
+    hipError_t err = hipSuccess;
+    for (Block& b : idle) {
+      hipError_t e = hipSetDevice(b.dev);
+      if (e == hipSuccess) e = hipEventSynchronize(b.done);
+      if (e == hipSuccess) e = hipFree(b.ptr);
+      (void)hipEventDestroy(b.done);
+      if (e != hipSuccess) err = e;
+    }
+    HIPCHK(hipSetDevice(dev));
+    HIPCHK(err);
+    return 0;
+  } catch (...) {
+    return fail(MCRT_EHIP, "mcrt_release_workspaces: host exception");
   }
 }
 
@@ -2661,7 +2858,7 @@ int peel_off(const mcrt_grid* grid, const void* rho_dev, double kappa, double g,
     std::memcpy(blob.data(), det.data(), sizeof(DetDev) * det.size());
     DeviceBlock blk;
     blk.st = st;
-    HIPCHK(hipMallocAsync(reinterpret_cast<void**>(&blk.ptr), bytes, st));
+    if (int e = blk.alloc(bytes)) return e;
     host::put_planes(*grid, P.G, blob.data() + off_pl, blk.ptr + off_pl);
     HIPCHK(hipMemcpyAsync(blk.ptr, blob.data(), off_rho, hipMemcpyHostToDevice, st));
     if (int e = brick_density(P.G, rho_dev, blk.ptr + off_rho, f32, st)) return e;
@@ -2708,7 +2905,7 @@ int dust_emission(const mcrt_grid* grid, const void* rho_dev, int precision, int
     std::vector<unsigned char> blob(off_t, 0);
     DeviceBlock blk;
     blk.st = st;
-    HIPCHK(hipMallocAsync(reinterpret_cast<void**>(&blk.ptr), bytes, st));
+    if (int e = blk.alloc(bytes)) return e;
     host::put_planes(*grid, P.G, blob.data(), blk.ptr);
     host::dust_constants(n_lambda, lambda, dlambda, kappa_abs, reinterpret_cast<double*>(blob.data() + off_a),
                          reinterpret_cast<double*>(blob.data() + off_b));
