@@ -267,7 +267,7 @@ struct TraceMem {
   const TraceParams& P;
   unsigned long long* res;
   __device__ R rho(int c) const { return rho_[c]; }
-  __device__ unsigned long long fetch() const { return wave_fetch(P.work, res, 256); }
+  __device__ unsigned long long fetch() const { return wave_fetch(P.work, res, P.run); }
   __device__ void ray(long long q, double o[3], double k[3]) const {
     for (int a = 0; a < 3; ++a) {
       o[a] = P.origin[3 * q + a];
@@ -291,7 +291,7 @@ struct PeelMem {
   const PeelParams& P;
   unsigned long long* res;
   __device__ R rho(int c) const { return rho_[c]; }
-  __device__ unsigned long long fetch() const { return wave_fetch(P.work, res, 256); }
+  __device__ unsigned long long fetch() const { return wave_fetch(P.work, res, P.run); }
   __device__ const DetDev& det(int d) const { return P.det[d]; }
   __device__ void position(long long e, double r[3]) const {
     for (int a = 0; a < 3; ++a) r[a] = P.pos[3 * e + a];
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))
   life_body<R, ADJ, GK, INST, true>(P, &tail);
 }
 
-template <typename R, int GK>
+template <typename R, int GK, int D>
 __global__ void __launch_bounds__(kBlock) k_trace(const TraceParams P) {
   __shared__ unsigned long long slots[kWavesPerBlock][2];
   TraceMem<R, GK> M{static_cast<const R*>(P.rho), P, wave_reservoir(slots)};
@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(kBlock) k_trace(const TraceParams P) {
     for (;;) {
       const int n_act = __popcll(__ballot(L.ry.active));
       if (n_act == 0 || n_live - n_act >= P.batch) break;
-      if (L.ry.active) trace_step(L, P, M);
+      if (L.ry.active) trace_step<R, decltype(M), D>(L, P, M);
     }
   }
   const unsigned long long total = wave_sum_u64(L.total), overflow = wave_sum_u64(L.overflow);
@@ -420,7 +420,7 @@ __global__ void __launch_bounds__(kBlock) k_trace(const TraceParams P) {
   }
 }
 
-template <typename R, int GK>
+template <typename R, int GK, int D>
 __global__ void __launch_bounds__(kBlock) k_peel(const PeelParams P) {
   __shared__ unsigned long long slots[kWavesPerBlock][2];
   PeelMem<R, GK> M{static_cast<const R*>(P.rho), P, wave_reservoir(slots)};
@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(kBlock) k_peel(const PeelParams P) {
     for (;;) {
       const int n_act = __popcll(__ballot(L.ry.active));
       if (n_act == 0 || n_live - n_act >= P.batch) break;
-      if (L.ry.active) peel_step(L, P, M);
+      if (L.ry.active) peel_step<R, decltype(M), D>(L, P, M);
     }
   }
 }
@@ -1592,6 +1592,35 @@ int launch_persistent(K kernel, const Params& P, hipStream_t st, int blocks_per_
   return 0;
 }
 
+// Fewer rays than two for every lane of k_trace's grid: the walks' latency
+// bounds the call.  Such rays walk kRayFew crossings per step -- 4096 rays
+// on the spiral's grid 514 -> 170 us with a run of 64 (below) -- and the others
+// kBlockWalk, whose fewer loads in flight thrash the L2 less (4e6 rays: 2.69
+// ms, 2.86 with eight).
+// Peel rays towards few frames share lines, so their line is further out
+// (1.1e6 rays on the spiral's grid 620 -> 578 us; 3e6 rays on 200^3
+// cells 2.27 ms with four crossings, 2.32 with eight).
+constexpr long long kFewRays = 1ll << 18, kFewPeels = 1ll << 21;
+constexpr int kRayFew = 2 * kBlockWalk;
+
+// Rays a wavefront of a ray kernel takes from the counter at a time: 256 for
+// long lists (few requests on one counter: 4e6 rays on 48 x 40 x 36 cells 627
+// us, 865 with 64), fewer where that would leave wavefronts without work
+// (4096 rays: 16 wavefronts walked 256 rays each, four after another; 154 us,
+// 81 with 64).
+unsigned ray_run(long long n) { return n < kFewRays ? 64u : (n < 4 * kFewRays ? 128u : 256u); }
+
+// Whether a call walks the caller's row-major densities themselves: few
+// rays, whose crossings are not worth a bricked copy of the grid, 10 us and
+// more (spiral's grid: 20000 rays 192 -> 182 us, 200000 rays 258 -> 300; 200^3
+// cells 20000 rays 204 -> 187, 60000 rays 203 -> 229).  A tree grid's cells have no
+// bricks and are never copied.
+bool walk_direct(const mcrt_grid& g, long long rays) {
+  if (g.tree_nodes > 0) return true;
+  const double crossings = (double)rays * ((double)g.nx + g.ny + g.nz) / 3.0;
+  return crossings < 1e6 + 0.5 * (double)g.nx * g.ny * g.nz;
+}
+
 // Launches the grid kind's variant of a persistent kernel.
 template <typename Params, typename R, typename K>
 int launch_by_kind(const Params& P, hipStream_t st, K regular, K rect, K tree, int blocks_per_cu = 0) {
@@ -1607,6 +1636,7 @@ int launch_by_kind(const Params& P, hipStream_t st, K regular, K rect, K tree, i
 // case: their lanes share lines, and their walk wants every wavefront it
 // can get (clumpy: 612 ms at 5 workgroups per CU, 982 at 2).
 constexpr int kTraceBlocksPerCu = 2;
+constexpr int kRowMajor = 0x1000;  // MCRT_BRICK(0, 0, 0): bricks of one cell, the caller's own order
 
 unsigned stream_blocks(long long n) { return (unsigned)std::min<long long>((n + kBlock - 1) / kBlock, 16384); }
 
@@ -2645,9 +2675,9 @@ int scratch_address(unsigned char** out) {
 
 // trace_path's work.  fixed = false: the device block is allocated on the
 // stream and freed there when the work ends; fixed = true: it is the
-// scratch array (sizes beyond it are rejected before any device work), and
-// the counters are cleared by a fill kernel rather than by the copy of the
-// tables, which only rectilinear and tree grids need.
+// scratch array (sizes beyond it are rejected before any device work).  The
+// tables of rectilinear and tree grids, which the call alone owns, are
+// copied from host memory.  The counters are cleared by a fill kernel.
 int trace_impl(const mcrt_grid* grid, const void* rho_dev, double kappa, int precision, int64_t n_rays,
                const double* origin_dev, const double* dir_dev, double* tau_dev, int32_t max_seg,
                int32_t* seg_cell_dev, double* seg_len_dev, int32_t* n_seg_dev, uint64_t* crossings_host,
@@ -2681,31 +2711,41 @@ int trace_impl(const mcrt_grid* grid, const void* rho_dev, double kappa, int pre
   P.seg_len = lists ? seg_len_dev : nullptr;
   P.n_seg = n_seg_dev;
   P.batch = kBatchQueue;
+  P.run = ray_run(n_rays);
+  const bool direct = walk_direct(*grid, n_rays);
+  if (direct)
+    if (int e = host::make_grid(*grid, host::elem_bytes(precision), kRowMajor, P.G)) return e;
   DeviceBlock blk;  // frees only what it allocated
   blk.st = st;
   unsigned char* base = nullptr;
   if (fixed) {
     if (int e = scratch_address(&base)) return e;
   } else {
-    if (int e = blk.alloc(bytes)) return e;
+    if (int e = blk.alloc(direct ? off_rho : bytes)) return e;
     base = blk.ptr;
   }
-  if (tables || !fixed) {
+  if (tables) {
     std::vector<unsigned char> blob(off_rho, 0);
     host::put_planes(*grid, P.G, blob.data() + 256, base + 256);
     HIPCHK(hipMemcpyAsync(base, blob.data(), off_rho, hipMemcpyHostToDevice, st));
   }
-  if (fixed) hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<unsigned*>(base), 64ll);
-  if (int e = brick_density(P.G, rho_dev, base + off_rho, f32, st)) return e;
-  P.rho = base + off_rho;
+  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<unsigned*>(base), 64ll);
+  if (!direct)
+    if (int e = brick_density(P.G, rho_dev, base + off_rho, f32, st)) return e;
+  P.rho = direct ? rho_dev : base + off_rho;
   P.work = reinterpret_cast<unsigned long long*>(base);
   P.counters = P.work + 1;
-  const int r = f32 ? launch_by_kind<TraceParams, float>(P, st, k_trace<float, kGridRegular>,
-                                                         k_trace<float, kGridRect>, k_trace<float, kGridTree>,
-                                                         kTraceBlocksPerCu)
-                    : launch_by_kind<TraceParams, double>(P, st, k_trace<double, kGridRegular>,
-                                                          k_trace<double, kGridRect>, k_trace<double, kGridTree>,
-                                                          kTraceBlocksPerCu);
+  const bool few = n_rays < kFewRays;
+  auto launch = [&](auto elem) -> int {
+    using R = decltype(elem);
+    return few ? launch_by_kind<TraceParams, R>(P, st, k_trace<R, kGridRegular, kRayFew>,
+                                                k_trace<R, kGridRect, kRayFew>, k_trace<R, kGridTree, kBlockWalk>,
+                                                kTraceBlocksPerCu)
+               : launch_by_kind<TraceParams, R>(P, st, k_trace<R, kGridRegular, kBlockWalk>,
+                                                k_trace<R, kGridRect, kBlockWalk>, k_trace<R, kGridTree, kBlockWalk>,
+                                                kTraceBlocksPerCu);
+  };
+  const int r = f32 ? launch(0.0f) : launch(0.0);
   if (r) return r;
   HIPCHK(hipGetLastError());
   if (crossings_host || lists) {
@@ -2847,13 +2887,14 @@ int peel_off(const mcrt_grid* grid, const void* rho_dev, double kappa, double g,
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     PeelParams P;
     std::memset(&P, 0, sizeof P);
-    if (int e = host::make_grid(*grid, host::elem_bytes(precision), 0, P.G)) return e;
+    const bool direct = walk_direct(*grid, n_events * n_det);
+    if (int e = host::make_grid(*grid, host::elem_bytes(precision), direct ? kRowMajor : 0, P.G)) return e;
     const bool f32 = precision == MCRT_PREC_FP32;
     std::vector<DetDev> det = host::make_dets(n_det, detectors, nullptr);
     const size_t off_cnt = align256(sizeof(DetDev) * det.size());
     const size_t off_pl = off_cnt + 256;
     const size_t off_rho = off_pl + host::plane_bytes(P.G, *grid);
-    const size_t bytes = off_rho + (size_t)P.G.ncell_pad * (f32 ? 4 : 8);
+    const size_t bytes = off_rho + (direct ? 0 : (size_t)P.G.ncell_pad * (f32 ? 4 : 8));
     std::vector<unsigned char> blob(off_rho, 0);
     std::memcpy(blob.data(), det.data(), sizeof(DetDev) * det.size());
     DeviceBlock blk;
@@ -2861,8 +2902,9 @@ int peel_off(const mcrt_grid* grid, const void* rho_dev, double kappa, double g,
     if (int e = blk.alloc(bytes)) return e;
     host::put_planes(*grid, P.G, blob.data() + off_pl, blk.ptr + off_pl);
     HIPCHK(hipMemcpyAsync(blk.ptr, blob.data(), off_rho, hipMemcpyHostToDevice, st));
-    if (int e = brick_density(P.G, rho_dev, blk.ptr + off_rho, f32, st)) return e;
-    P.rho = blk.ptr + off_rho;
+    if (!direct)
+      if (int e = brick_density(P.G, rho_dev, blk.ptr + off_rho, f32, st)) return e;
+    P.rho = direct ? rho_dev : blk.ptr + off_rho;
     P.kappa = kappa;
     P.g = g;
     P.n_events = n_events;
@@ -2874,10 +2916,16 @@ int peel_off(const mcrt_grid* grid, const void* rho_dev, double kappa, double g,
     P.images = images_dev;
     P.work = reinterpret_cast<unsigned long long*>(blk.ptr + off_cnt);
     P.batch = kBatchQueue;
-    const int r = f32 ? launch_by_kind<PeelParams, float>(P, st, k_peel<float, kGridRegular>,
-                                                          k_peel<float, kGridRect>, k_peel<float, kGridTree>)
-                      : launch_by_kind<PeelParams, double>(P, st, k_peel<double, kGridRegular>,
-                                                           k_peel<double, kGridRect>, k_peel<double, kGridTree>);
+    P.run = ray_run(n_events * n_det);
+    const bool few = n_events * n_det < kFewPeels;
+    auto launch = [&](auto elem) -> int {
+      using R = decltype(elem);
+      return few ? launch_by_kind<PeelParams, R>(P, st, k_peel<R, kGridRegular, kRayFew>, k_peel<R, kGridRect, kRayFew>,
+                                                 k_peel<R, kGridTree, kBlockWalk>)
+                 : launch_by_kind<PeelParams, R>(P, st, k_peel<R, kGridRegular, kBlockWalk>,
+                                                 k_peel<R, kGridRect, kBlockWalk>, k_peel<R, kGridTree, kBlockWalk>);
+    };
+    const int r = f32 ? launch(0.0f) : launch(0.0);
     if (r) return r;
     HIPCHK(hipGetLastError());
     return 0;

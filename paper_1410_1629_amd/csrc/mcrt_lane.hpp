@@ -837,6 +837,7 @@ struct TraceParams {
   unsigned long long* work;
   unsigned long long* counters;  // [0] segments, [1] rays over max_seg
   int batch;
+  unsigned run;  // rays a wavefront takes at a time
 };
 
 template <typename R>
@@ -883,14 +884,16 @@ MCRT_HD void trace_events(TraceLane<R>& L, const TraceParams& P, Mem& M) {
   }
 }
 
-template <typename R, class Mem>
+// D crossings per step: kBlockWalk, or twice as many for a batch of few rays,
+// which then waits for half as many loads (k_trace).
+template <typename R, class Mem, int D = kBlockWalk>
 MCRT_HD void trace_step(TraceLane<R>& L, const TraceParams& P, Mem& M) {
   Ray<R>& ry = L.ry;
-  WalkBlock<kBlockWalk, R> b;
+  WalkBlock<D, R> b;
   ray_next_block(ry, b, P.G, M);
   const R kap = (R)P.kappa;
 #pragma unroll
-  for (int d = 0; d < kBlockWalk; ++d) {
+  for (int d = 0; d < D; ++d) {
     if (d >= b.n) break;
     R seg = b.tend[d] - ry.t;
     const bool pos = seg > R(0);
@@ -918,6 +921,7 @@ struct PeelParams {
   double* images;
   unsigned long long* work;
   int batch;
+  unsigned run;  // rays a wavefront takes at a time
 };
 
 template <typename R>
@@ -969,15 +973,15 @@ MCRT_HD void peel_events(PeelLane<R>& L, const PeelParams& P, Mem& M) {
   }
 }
 
-template <typename R, class Mem>
+template <typename R, class Mem, int D = kBlockWalk>
 MCRT_HD void peel_step(PeelLane<R>& L, const PeelParams& P, Mem& M) {
   Ray<R>& ry = L.ry;
-  WalkBlock<kBlockWalk, R> b;
+  WalkBlock<D, R> b;
   ray_next_block(ry, b, P.G, M);
   const R kap = (R)P.kappa;
   // sub-steps past b.n masked, not skipped: the block's loads stay in flight together
 #pragma unroll
-  for (int d = 0; d < kBlockWalk; ++d) {
+  for (int d = 0; d < D; ++d) {
     const R tm = b.tend[d] > ry.tmax ? ry.tmax : b.tend[d];
     const R seg = tm - ry.t;
     const bool pos = d < b.n && seg > R(0);
