@@ -485,23 +485,113 @@ struct DustDev {
 
 MCRT_HD double dust_step() { return log(kDustTmax) / kDustTable; }
 
+// e^u - 1 for 0 <= u < 700, within 1.6 units of 2^-53: u = n ln 2 + r with |r|
+// <= ln 2 / 2, e^r - 1 = r + w by its Taylor series up to r^14 / 14! (below
+// 1e-17 of it), and 2^n (r + w) + (2^n - 1) with the first sum's remainder.
+MCRT_HD double expm1_pos(double u) {
+  const double n = rint(u * 1.4426950408889634);
+  const double v = fma(n, -6.93147180369123816490e-01, u);  // ln 2 in two parts
+  const double r = fma(n, -1.9082149292705877e-10, v);
+  const double low = fma(n, -1.9082149292705877e-10, v - r);
+  double q = 1.0 / 87178291200.0;  // 1 / 14!
+  constexpr double f[] = {1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0,
+                          1.0 / 40320.0,      1.0 / 5040.0,      1.0 / 720.0,      1.0 / 120.0,     1.0 / 24.0,
+                          1.0 / 6.0,          0.5};
+#pragma unroll
+  for (int i = 0; i < 12; ++i) q = fma(q, r, f[i]);
+  const double w = fma(r * r, q, low);
+  const double s = ldexp(1.0, (int)n), c = s - 1.0;
+  const double h = fma(s, r, c);
+  return h + fma(s, w, fma(s, r, c - h));
+}
+
+// a / d for normal d, rounded once (a reciprocal by Newton's method, then a
+// correction by the remainder): on the device a third of the instructions
+// of a division, which also handles what cannot occur here.  `inv` receives
+// 1 / d to within an ulp.
+MCRT_HD double div_normal(double a, double d, double& inv) {
+#ifdef __HIP_DEVICE_COMPILE__
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(fma(-d, y, 1.0), y, y);
+  y = fma(fma(-d, y, 1.0), y, y);
+  inv = y;
+  const double t = a * y;
+  return fma(fma(-d, t, a), y, t);
+#else
+  inv = 1.0 / d;
+  return a / d;
+#endif
+}
+
+// One wavelength's a / (exp(b / T) - 1), with u = b / T and 1 / (exp(u) - 1);
+// invT = 1 / T.  (A relative error e of u is one of u e in the result, so u is
+// rounded once too.)  Factors that could leave the normal range take the
+// plain functions.
+MCRT_HD double dust_term(double a, double b, double T, double invT, double& u, double& inv) {
+  u = b * invT;
+  if (!(u > 1e-30 && u < 700.0 && a > 1e-200 && a < 1e200)) {
+    u = b / T;
+    const double em = expm1(u);
+    inv = 1.0 / em;
+    return a / em;
+  }
+  u = fma(fma(-u, T, b), invT, u);
+  return div_normal(a, expm1_pos(u), inv);
+}
+
 // P(T) and dP/dlnT.
 MCRT_HD void dust_sum(const DustDev& D, double T, double& P, double& dP) {
   P = 0.0;
   dP = 0.0;
+  const double invT = 1.0 / T;
   for (int i = 0; i < D.nl; ++i) {
-    const double u = D.b[i] / T, em = expm1(u), t = D.a[i] / em;
+    double u, inv;
+    const double t = dust_term(D.a[i], D.b[i], T, invT, u, inv);
     P += t;
-    dP += t * u * (1.0 + 1.0 / em);
+    dP += t * u * (1.0 + inv);
   }
 }
 
+// x = ln T at ln P = ly from the table's entries k-2 .. k+3 (lnP[k] < ly <=
+// lnP[k+1]): the polynomial of degree 5 in ln P through them (Neville's
+// scheme); its error, (h/2)^6-sized, is below 1e-9 where ln P is smooth on the
+// scale of the table's spacing h.  False where the six entries do not exist
+// or one is not finite.
+MCRT_HD bool dust_guess(const DustDev& D, int k, double ly, double h, double& x) {
+  if (k < 2 || k + 3 > kDustTable) return false;
+  double p[6], v[6];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    p[j] = D.lnP[k - 2 + j];
+    v[j] = (k - 2 + j) * h;
+  }
+  if (!std::isfinite(p[0])) return false;  // the others are larger, and the last below +inf with ly
+#pragma unroll
+  for (int m = 1; m < 6; ++m)
+#pragma unroll
+    for (int j = 0; j + m < 6; ++j) {
+      double inv;
+      v[j] = v[j] + div_normal((ly - p[j]) * (v[j + 1] - v[j]), p[j + m] - p[j], inv);
+    }
+  x = v[0];
+  return true;
+}
+
 // Equilibrium temperature for y > 0 (kDustTmin or kDustTmax where the root
-// lies outside).
-MCRT_HD double dust_temperature(const DustDev& D, double y) {
+// lies outside), and P there.  The Newton step is taken in T itself, so that
+// P(T) follows to first order from the sums before the last step (its square
+// is below rounding): one pass over the wavelengths where the guess is good.
+MCRT_HD double dust_temperature(const DustDev& D, double y, double& S) {
   const double ly = log(y), h = dust_step();
-  if (!(ly > D.lnP[0])) return kDustTmin;
-  if (!(ly < D.lnP[kDustTable])) return kDustTmax;
+  double dS;
+  if (!(ly > D.lnP[0])) {
+    dust_sum(D, kDustTmin, S, dS);
+    return kDustTmin;
+  }
+  if (!(ly < D.lnP[kDustTable])) {
+    dust_sum(D, kDustTmax, S, dS);
+    return kDustTmax;
+  }
   int k = 0, hi_k = kDustTable - 1;  // the last k with lnP[k] < ly
   while (k < hi_k) {
     const int mid = (k + hi_k + 1) >> 1;
@@ -512,24 +602,35 @@ MCRT_HD double dust_temperature(const DustDev& D, double y) {
   }
   double lo = k * h, hi = (k + 1) * h;
   const double p0 = D.lnP[k], p1 = D.lnP[k + 1];
-  double x = std::isfinite(p0) ? lo + (ly - p0) / (p1 - p0) * h : 0.5 * (lo + hi);
+  double x;
+  if (!dust_guess(D, k, ly, h, x)) x = std::isfinite(p0) ? lo + (ly - p0) / (p1 - p0) * h : 0.5 * (lo + hi);
   if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);
+  double T = exp(x);
   for (int it = 0; it < 64; ++it) {
-    double P, dP;
-    dust_sum(D, exp(x), P, dP);
-    const double f = log(P) - ly;
+    dust_sum(D, T, S, dS);
+    // ln S - ln y; near the root from the difference, which does not round with ln y's size
+    const double f = S > 0.5 * y && S < 2.0 * y ? log1p((S - y) / y) : log(S) - ly;
     if (f == 0.0) break;
     if (f < 0.0)
       lo = x;
     else
       hi = x;
-    double xn = x - f * P / dP;
+    const double slope = dS / S, d = -f / slope;
+    if (fabs(d) * fmax(slope, 1.0) <= 1e-8) {
+      const double Tn = fma(T, d, T), r = (Tn - T) / T;
+      S = fma(dS, r, S);
+      return Tn;
+    }
+    double xn = x + d;
     if (!(xn > lo && xn < hi)) xn = 0.5 * (lo + hi);
-    const bool last = fabs(xn - x) <= 1e-15 * (1.0 + x) || hi - lo <= 1e-15 * (1.0 + hi);
     x = xn;
-    if (last) break;
+    T = exp(x);
+    if (hi - lo <= 1e-15 * (1.0 + hi)) {
+      dust_sum(D, T, S, dS);
+      break;
+    }
   }
-  return exp(x);
+  return T;
 }
 
 MCRT_HD double dust_table_entry(const DustDev& D, int k) {
@@ -562,14 +663,17 @@ MCRT_HD void dust_cell(const DustParams& P, int m) {
   const double M = (double)static_cast<const R*>(P.rho)[m] * ((hi[0] - lo[0]) * (hi[1] - lo[1]) * (hi[2] - lo[2]));
   double T = 0.0, scale = 0.0;
   if (L > 0.0 && M > 0.0) {
-    T = dust_temperature(P.D, L / (P.emissivity * M));
-    double S, dS;
-    dust_sum(P.D, T, S, dS);
+    double S;
+    T = dust_temperature(P.D, L / (P.emissivity * M), S);
     scale = S > 0.0 ? L / S : 0.0;
   }
   if (P.temperature) P.temperature[m] = T;
-  for (int i = 0; i < P.D.nl; ++i)
-    P.emission[(long long)i * nc + m] = scale > 0.0 ? scale * (P.D.a[i] / expm1(P.D.b[i] / T)) : 0.0;
+  const double invT = 1.0 / T;
+  for (int i = 0; i < P.D.nl; ++i) {
+    double u, inv, e = 0.0;
+    if (scale > 0.0) e = scale * dust_term(P.D.a[i], P.D.b[i], T, invT, u, inv);
+    P.emission[(long long)i * nc + m] = e;
+  }
 }
 
 // ---------------------------------------------------------------------------
