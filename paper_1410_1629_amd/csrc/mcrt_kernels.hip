@@ -798,9 +798,9 @@ __global__ void __launch_bounds__(kSortThreads) k_hist(const unsigned* __restric
 }
 
 // Runs of one first key at least this long skip the second level: its one
-// workgroup per run would walk such a run alone, some 3 us per 256 rays (a
+// workgroup per run would walk such a run alone, some 0.14 us per 256 rays (a
 // point source's emission peel-offs all start at one place, one pixel and
-// one depth: 1e7 rays, 33 ms), so k_scatter places their rays in the first
+// one depth: 1e7 rays, 5 ms), so k_scatter places their rays in the first
 // level's order itself.  Shorter runs keep the second level, whose order
 // the peel walks need (the clumpy disk's busiest tiles hold a few 1e5 rays
 // per chunk; with a bound of 65536 its peel walks took 1052 ms, not 478).
@@ -955,10 +955,32 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_add(unsigned* __restrict_
     if (base + i < n) starts[base + i] += off;
 }
 
+// Adds 1 to h[s] for every lane with `on` and returns the lane's own place
+// there.  The lanes that share the first one's counter take their places
+// with one atomic: LDS serves the lanes of one address one after another, and
+// a run of one pixel and depth has all 64 there.
+__device__ __forceinline__ unsigned take_place(unsigned* h, unsigned s, bool on) {
+  const unsigned long long all = __ballot(on);
+  if (!all) return 0u;
+  const int first = __ffsll((long long)all) - 1;
+  const unsigned s0 = (unsigned)__builtin_amdgcn_readlane((int)s, first);
+  const unsigned long long same = __ballot(on && s == s0);
+  const bool mine = (same >> __lane_id()) & 1ull;
+  unsigned q = 0;
+  if (on && (!mine || __lane_id() == first)) q = atomicAdd(h + s, mine ? (unsigned)__popcll(same) : 1u);
+  const unsigned q0 = (unsigned)__builtin_amdgcn_readlane((int)q, first);
+  return mine ? q0 + __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u)) : q;
+}
+
 // Workgroup k sorts the run [starts of key k, starts of key k + 1) of idx
 // by subs (the pixel inside the tile, then the depth) into perm.  Only the
 // n_sub counters the frames' second keys can reach are cleared and scanned
 // (a 128^2 frame has one-pixel tiles and 6-bit second keys: 64 of 16384).
+// A long run has one workgroup only, so each thread holds kRefinePer rays in
+// flight per turn: with one, and an atomic per ray, a call whose longest run
+// holds the 1e6 emission rays of a point source took 1.77 ms here, now 0.54
+// (1e5 rays: 0.19 -> 0.075 ms; many short runs are unchanged).
+constexpr int kRefinePer = 8;
 __global__ void __launch_bounds__(kRefineThreads) k_refine(const unsigned* __restrict__ starts,
                                                            const unsigned* __restrict__ idx,
                                                            const unsigned short* __restrict__ subs,
@@ -972,7 +994,16 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine(const unsigned* __res
   if (hi - lo >= kHotRun) return;  // placed by k_scatter
   for (int i = threadIdx.x; i < n_sub; i += kRefineThreads) h[i] = 0u;
   __syncthreads();
-  for (unsigned i = lo + threadIdx.x; i < hi; i += kRefineThreads) atomicAdd(h + subs[i], 1u);
+  for (unsigned b = lo; b < hi; b += kRefineThreads * kRefinePer) {
+    unsigned s[kRefinePer];
+#pragma unroll
+    for (int r = 0; r < kRefinePer; ++r) {
+      const unsigned i = b + (unsigned)r * kRefineThreads + threadIdx.x;
+      s[r] = i < hi ? subs[i] : kNoKey;
+    }
+#pragma unroll
+    for (int r = 0; r < kRefinePer; ++r) take_place(h, s[r], s[r] != kNoKey);
+  }
   __syncthreads();
   // thread t scans counters [t per, (t + 1) per) (n_sub and the threads are powers of two)
   const int per = n_sub >= kRefineThreads ? n_sub / kRefineThreads : 1;
@@ -986,7 +1017,20 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine(const unsigned* __res
     run += c;
   }
   __syncthreads();
-  for (unsigned i = lo + threadIdx.x; i < hi; i += kRefineThreads) perm[atomicAdd(h + subs[i], 1u)] = idx[i];
+  for (unsigned b = lo; b < hi; b += kRefineThreads * kRefinePer) {
+    unsigned s[kRefinePer], v[kRefinePer];
+#pragma unroll
+    for (int r = 0; r < kRefinePer; ++r) {
+      const unsigned i = b + (unsigned)r * kRefineThreads + threadIdx.x;
+      s[r] = i < hi ? subs[i] : kNoKey;
+      v[r] = i < hi ? idx[i] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kRefinePer; ++r) {
+      const unsigned q = take_place(h, s[r], s[r] != kNoKey);
+      if (s[r] != kNoKey) perm[q] = v[r];
+    }
+  }
 }
 
 constexpr int kBundleThreads = 512;
