@@ -1354,18 +1354,30 @@ struct AttMem {
   }
 };
 
-// Persistent: a lane that has finished its package takes the next one from
-// the chunk's work counter (packages differ widely in their number of
-// events, and a wavefront of one package per lane lasts as long as its
-// longest one).
-template <typename S, int GK>
-__global__ void __launch_bounds__(kBlock) k_attached(const RunParams P) {
+// Persistent: the lanes take packages from the chunk's work counter.
+//
+// Bound by the latency of the walks' loads and by the legs' deposits, one
+// FP64 atomic per crossing (64^3 cells, 1e6 packages: 2.6e8 of them, some 12
+// ms at the memory side's 2.2e10 per second).  Free of a limit the kernel
+// takes 262 registers, so one wavefront per SIMD, which does nothing while it
+// waits; held to two (256 registers, two doubles spilled) the walks of one
+// run during the other's waits: 22.7 -> 16.5 ms (three: 15.8 there, but 2.36
+// against 1.96 ms with 2e4 packages).  A call of fewer packages than one
+// wavefront per SIMD has lanes is over with its longest packages, which run
+// faster alone and unspilled: 2e4 packages take 1.75 ms that way and 1.95 in
+// two wavefronts, 1e5 take 3.33 and 2.95; launch_attached draws the line.
+// Between one and two wavefronts' lanes every wavefront takes its even share.
+template <typename S, int GK, int WAVES>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WAVES))) k_attached(const RunParams P) {
   __shared__ unsigned long long slots[kWavesPerBlock][2], job_slots[kWavesPerBlock][2];
   unsigned long long* const res = wave_reservoir(slots);
   AttMem<S, GK> M{static_cast<const S*>(P.rho), P, wave_reservoir(job_slots)};
   AttCounts c;
-  for (;;) {
-    const unsigned long long k = wave_fetch(P.work, res, 64);
+  const unsigned long long waves = (unsigned long long)gridDim.x * kWavesPerBlock;
+  const unsigned long long share = (P.n_chunk + waves - 1) / waves;
+  const int lanes = WAVES > 1 && share < 64 ? (int)share : 64;
+  while (__lane_id() < lanes) {
+    const unsigned long long k = wave_fetch(P.work, res, (unsigned)lanes);
     if (k >= P.n_chunk) break;
     attached_item<double>(P, M, P.item0 + k, (int)k, c);
   }
@@ -2178,18 +2190,31 @@ void launch_life_c(const RunParams& P, int nblk, hipStream_t st) {
 }
 
 // The attached gradient's kernel over one chunk (its work counter reset by
-// the caller): a persistent grid; f32: the densities are stored in FP32.
+// the caller): a persistent grid of one wavefront per SIMD for fewer items
+// than that has lanes, else of two (see k_attached).
+template <typename S, int GK>
+int launch_attached_k(const RunParams& P, hipStream_t st) {
+  int one = 0;
+  if (int e = persistent_grid(k_attached<S, GK, 1>, 0, &one)) return e;
+  if (P.n_chunk < (unsigned long long)one * kBlock) {
+    hipLaunchKernelGGL((k_attached<S, GK, 1>), dim3(one), dim3(kBlock), 0, st, P);
+    return 0;
+  }
+  return launch_persistent(k_attached<S, GK, 2>, P, st);
+}
+
+// f32: the densities are stored in FP32.
 int launch_attached(const RunParams& P, bool f32, hipStream_t st) {
   const int kind = P.G.kind;
   int e;
   if (f32)
-    e = kind == kGridRect   ? launch_persistent(k_attached<float, kGridRect>, P, st)
-        : kind == kGridTree ? launch_persistent(k_attached<float, kGridTree>, P, st)
-                            : launch_persistent(k_attached<float, kGridRegular>, P, st);
+    e = kind == kGridRect   ? launch_attached_k<float, kGridRect>(P, st)
+        : kind == kGridTree ? launch_attached_k<float, kGridTree>(P, st)
+                            : launch_attached_k<float, kGridRegular>(P, st);
   else
-    e = kind == kGridRect   ? launch_persistent(k_attached<double, kGridRect>, P, st)
-        : kind == kGridTree ? launch_persistent(k_attached<double, kGridTree>, P, st)
-                            : launch_persistent(k_attached<double, kGridRegular>, P, st);
+    e = kind == kGridRect   ? launch_attached_k<double, kGridRect>(P, st)
+        : kind == kGridTree ? launch_attached_k<double, kGridTree>(P, st)
+                            : launch_attached_k<double, kGridRegular>(P, st);
   if (e) return e;
   HIPCHK(hipGetLastError());
   return 0;
