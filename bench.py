@@ -75,8 +75,8 @@ KERNELS = {
     "life_adjoint": "void mcrt::k_life<float, true, 0, false>(mcrt::RunParams)",
     "peel_tau_adjoint": "void mcrt::k_peeltau<float, true, 0, false, true>(mcrt::PeelJobParams)",
     "peel_deposit": "void mcrt::k_peeldep<float, 0, false>(mcrt::PeelJobParams)",
-    "trace": "void mcrt::k_trace<float, 0>(mcrt::TraceParams)",
-    "attached": "void mcrt::k_attached<float, 0>(mcrt::RunParams)",
+    "trace": "void mcrt::k_trace<float, 0, 4>(mcrt::TraceParams)",
+    "attached": "void mcrt::k_attached<float, 0, 2>(mcrt::RunParams)",
 }
 # the attached gradient's workspace: 11 FP64 values per event, written in the
 # forward sweep and read back in the reverse sweep
