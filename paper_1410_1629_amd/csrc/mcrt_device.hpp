@@ -552,6 +552,17 @@ MCRT_HD void dust_sum(const DustDev& D, double T, double& P, double& dP) {
   }
 }
 
+// P(T) of the very terms that the cell's spectrum is made of (dust_cell):
+// their rounding, up to u units of 2^-53 where b/T = u, then cancels in the
+// normalised spectrum, whose sum is the absorbed luminosity to within the
+// rounding of the sum itself.
+MCRT_HD double dust_total(const DustDev& D, double T) {
+  const double invT = 1.0 / T;
+  double S = 0.0, u, inv;
+  for (int i = 0; i < D.nl; ++i) S += dust_term(D.a[i], D.b[i], T, invT, u, inv);
+  return S;
+}
+
 // x = ln T at ln P = ly from the table's entries k-2 .. k+3 (lnP[k] < ly <=
 // lnP[k+1]): the polynomial of degree 5 in ln P through them (Neville's
 // scheme); its error, (h/2)^6-sized, is below 1e-9 where ln P is smooth on the
@@ -578,20 +589,11 @@ MCRT_HD bool dust_guess(const DustDev& D, int k, double ly, double h, double& x)
 }
 
 // Equilibrium temperature for y > 0 (kDustTmin or kDustTmax where the root
-// lies outside), and P there.  The Newton step is taken in T itself, so that
-// P(T) follows to first order from the sums before the last step (its square
-// is below rounding): one pass over the wavelengths where the guess is good.
-MCRT_HD double dust_temperature(const DustDev& D, double y, double& S) {
+// lies outside): one pass over the wavelengths where the guess is good.
+MCRT_HD double dust_temperature(const DustDev& D, double y) {
   const double ly = log(y), h = dust_step();
-  double dS;
-  if (!(ly > D.lnP[0])) {
-    dust_sum(D, kDustTmin, S, dS);
-    return kDustTmin;
-  }
-  if (!(ly < D.lnP[kDustTable])) {
-    dust_sum(D, kDustTmax, S, dS);
-    return kDustTmax;
-  }
+  if (!(ly > D.lnP[0])) return kDustTmin;
+  if (!(ly < D.lnP[kDustTable])) return kDustTmax;
   int k = 0, hi_k = kDustTable - 1;  // the last k with lnP[k] < ly
   while (k < hi_k) {
     const int mid = (k + hi_k + 1) >> 1;
@@ -607,6 +609,7 @@ MCRT_HD double dust_temperature(const DustDev& D, double y, double& S) {
   if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);
   double T = exp(x);
   for (int it = 0; it < 64; ++it) {
+    double S, dS;
     dust_sum(D, T, S, dS);
     // ln S - ln y; near the root from the difference, which does not round with ln y's size
     const double f = S > 0.5 * y && S < 2.0 * y ? log1p((S - y) / y) : log(S) - ly;
@@ -616,19 +619,12 @@ MCRT_HD double dust_temperature(const DustDev& D, double y, double& S) {
     else
       hi = x;
     const double slope = dS / S, d = -f / slope;
-    if (fabs(d) * fmax(slope, 1.0) <= 1e-8) {
-      const double Tn = fma(T, d, T), r = (Tn - T) / T;
-      S = fma(dS, r, S);
-      return Tn;
-    }
+    if (fabs(d) * fmax(slope, 1.0) <= 1e-8) return fma(T, d, T);
     double xn = x + d;
     if (!(xn > lo && xn < hi)) xn = 0.5 * (lo + hi);
     x = xn;
     T = exp(x);
-    if (hi - lo <= 1e-15 * (1.0 + hi)) {
-      dust_sum(D, T, S, dS);
-      break;
-    }
+    if (hi - lo <= 1e-15 * (1.0 + hi)) break;
   }
   return T;
 }
@@ -663,8 +659,8 @@ MCRT_HD void dust_cell(const DustParams& P, int m) {
   const double M = (double)static_cast<const R*>(P.rho)[m] * ((hi[0] - lo[0]) * (hi[1] - lo[1]) * (hi[2] - lo[2]));
   double T = 0.0, scale = 0.0;
   if (L > 0.0 && M > 0.0) {
-    double S;
-    T = dust_temperature(P.D, L / (P.emissivity * M), S);
+    T = dust_temperature(P.D, L / (P.emissivity * M));
+    const double S = dust_total(P.D, T);
     scale = S > 0.0 ? L / S : 0.0;
   }
   if (P.temperature) P.temperature[m] = T;

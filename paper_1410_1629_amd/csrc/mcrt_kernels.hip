@@ -1663,12 +1663,17 @@ __global__ void k_dust_table(DustDev D, double* __restrict__ lnP) {
   if (k <= kDustTable) lnP[k] = dust_table_entry(D, k);
 }
 
-// Bound by FP64 instructions: two passes over the wavelengths per cell, one
-// that finds the temperature (dust_temperature) and one that writes the
-// spectrum, some 40 instructions a term.  Before, five passes of expm1 and
-// three divisions a term: 2^21 cells x 100 wavelengths 2.12 -> 1.0-1.1 ms (0.37 ms
-// for its 1.7 GB at a copy's rate).  Against an 80-bit reference, 3-3000 K:
-// temperatures 3.7e-16 -> 2.7e-17, spectra 8.6e-16 -> 3.3e-16.
+// Bound by FP64 instructions: three passes over the wavelengths per cell, one
+// that finds the temperature (dust_temperature), one that sums the spectrum
+// there and one that writes it, some 40 instructions a term.  Before, five
+// passes of expm1 and three divisions a term: 2^21 cells x 100 wavelengths
+// 2.13 -> 1.41 ms (0.36 ms for its 1.7 GB at a copy's rate).  Without the
+// second pass -- the sum carried over to first order from the Newton step --
+// it took 1.02 ms, and a cell's sum missed what it had absorbed by up to
+// 5.5e-14 where a Wien term lies beside a Rayleigh-Jeans one.  Against an
+// 80-bit reference, 3-3000 K, 2 to 100 random wavelengths of 0.1-1000 um,
+// largest relative errors then -> now: temperatures 9.9e-15 -> 5.7e-16, terms
+// 3.3e-12 -> 2.0e-13, a cell's sum 1.4e-15 -> 1.6e-15 (means 2.4e-16 both).
 template <typename R, int GK>
 __global__ void __launch_bounds__(kBlock) k_dust_emission(DustParams P) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
