@@ -1943,6 +1943,18 @@ bool stream_capturing(hipStream_t st) {
   return c != hipStreamCaptureStatusNone;
 }
 
+// While some stream of the process is being recorded into a graph in the
+// global mode, a query of an event, a wait of the host or a free ends that
+// recording, whatever stream they are about.  The store's own are none of the
+// recording's business, so its thread takes the relaxed mode for them.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+
 // The device's free memory, counting the idle blocks (a call may take them
 // or give them back).
 int free_memory(size_t* free_b) {
@@ -1962,6 +1974,7 @@ struct DeviceBlock {
     int dev = 0;
     HIPCHK(hipGetDevice(&dev));
     const bool keep = !stream_capturing(st);
+    const RelaxedCapture relaxed;
     if (keep) {
       if (block_store().take(bytes, dev, st, b)) {
         ptr = b.ptr;
@@ -2923,6 +2936,7 @@ uint64_t mcrt_tape_bytes(const mcrt_optics* optics, int n_det, const mcrt_opts* 
 int mcrt_release_workspaces(void) {
   try {
     mcrt::host::last_error().clear();
+    const RelaxedCapture relaxed;
     std::vector<Block> idle;
     block_store().drop(-1, SIZE_MAX, idle);
     int dev = 0;
