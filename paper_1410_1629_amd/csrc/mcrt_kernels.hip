@@ -450,9 +450,11 @@ struct LegMem {
   static constexpr int kGrid = GK;
   static constexpr bool kLut = LUT;
   const R* __restrict__ rho_;
+  const LamDev* lam_;
   const int* lut = nullptr;
   int o1 = 0, o2 = 0;
   __device__ R rho(int c) const { return rho_[c]; }
+  __device__ const LamDev& lam(int l) const { return lam_[l]; }
   __device__ int lut_addr(const int i[3]) const { return lut[i[0] + 1] + lut[o1 + i[1]] + lut[o2 + i[2]]; }
   __device__ void fill_lut(int* l, const GridDev& G) {  // by the whole workgroup; the launch checks the size
     const int tot = lut_cells(G);
@@ -535,44 +537,20 @@ __global__ void __launch_bounds__(kBlock) k_leg(const StageParams S) {
   __shared__ int lut[LUT ? kLutCells : 1];
   const RunParams& P = S.P;
   const GridDev& G = P.G;
-  LegMem<R, GK, LUT> M{static_cast<const R*>(P.rho)};
+  LegMem<R, GK, LUT> M{static_cast<const R*>(P.rho), P.lam};
   if constexpr (LUT) M.fill_lut(lut, G);
   PkgFeed feed{bufs[threadIdx.x / 64]};
   Leg<R> L;
-  L.ry.active = false;
-  L.mode = kLegPath;
-  double T = 0.0, tau_s = 0.0;
-  R kapR = R(0);
-  unsigned q = 0, slot = 0, lam = 0;
+  leg_init(L);
+  unsigned q = 0;
   bool busy = false;
   unsigned long long x_path = 0, x_loc = 0;
   for (;;) {
     if (busy && !L.ry.active) {
-      const StagePkg& p = S.in[q];
-      if (L.mode == kLegPath) {
-        T = (double)L.ry.tau;
-        if (T == 0.0) {  // nothing to interact with: the package leaves
-          S.leg[q] = StageLeg{0.0, 0.0};
-          busy = false;
-        } else {
-          tau_s = forced_depth(P, slot, lam, S.n, T);
-          L.tau_sR = (R)tau_s;
-          L.found = false;
-          L.mode = kLegLocate;
-          leg_restart<R, GK>(L, G, p.r, p.k);
-        }
-      } else if (L.found || L.mode == kLegLast) {  // the interaction point
-        double s = L.ry.tin + L.last;
-        if (L.found)
-          s = ray_cell_entry64<R, GK>(L.ry, G, p.r, p.k) +
-              (tau_s - (double)L.tau_prev) / (P.lam[lam].kappa * (double)L.rho_hit);
-        S.leg[q] = StageLeg{T, s};
+      StageLeg done;
+      if (leg_end<R, GK>(L, P, M, S.n, S.in[q], done)) {
+        S.leg[q] = done;
         busy = false;
-      } else {  // tau_s reached the total by rounding
-        L.mode = kLegLast;
-        L.tau_sR = R(INFINITY);
-        L.last = 0.0;
-        leg_restart<R, GK>(L, G, p.r, p.k);
       }
     }
     bool want = !busy;
@@ -580,14 +558,7 @@ __global__ void __launch_bounds__(kBlock) k_leg(const StageParams S) {
     feed.take(S, count, want, p, q);
     if (!busy && !want) {
       busy = true;
-      slot = p.slot;
-      lam = p.lam;
-      kapR = (R)P.lam[lam].kappa;
-      L.mode = kLegPath;
-      L.found = false;
-      L.tau_sR = R(INFINITY);
-      L.comp = R(0);
-      ray_begin<R, GK>(L.ry, G, p.r, p.k);
+      leg_begin<R, GK>(L, G, M, p);
     }
     const int n_busy = __popcll(__ballot(busy));
     if (n_busy == 0) break;
@@ -595,7 +566,7 @@ __global__ void __launch_bounds__(kBlock) k_leg(const StageParams S) {
       const int n_act = __popcll(__ballot(L.ry.active));
       if (n_act == 0 || n_busy - n_act >= P.batch) break;
       if (L.ry.active) {
-        const unsigned x = leg_step(L, G, kapR, M);
+        const unsigned x = leg_step(L, G, M);
         if (L.mode == kLegPath)
           x_path += x;
         else if (L.mode == kLegLocate)

@@ -123,10 +123,22 @@ struct Leg {
   Ray<R, double> ry;
   int mode;
   bool found;
+  unsigned slot, lam;
+  double T, tau_s;
+  R kapR;
   R tau_sR;  // kLegPath, kLegLast: +inf
   R comp, tau_prev, rho_hit;
   double last;  // kLegLast: end time of the last absorbing segment so far
 };
+
+template <typename R>
+MCRT_HD void leg_init(Leg<R>& L) {
+  L.ry.active = false;
+  L.mode = kLegPath;
+  L.slot = L.lam = 0;
+  L.T = L.tau_s = 0.0;
+  L.kapR = R(0);
+}
 
 // Back to the start of the walk: the indices step back by the planes
 // crossed, the plane times stay.  (A tree walk keeps its point and leaf, so
@@ -158,9 +170,10 @@ MCRT_HD void leg_restart(Leg<R>& L, const GridDev& G, const double r[3], const d
 // before the search ends, so that the block's density loads stay in flight
 // together; the block that holds the point is gone through again.  Returns the positive-length crossings.
 template <typename R, class Mem>
-MCRT_HD unsigned leg_step(Leg<R>& L, const GridDev& G, R kapR, Mem& M) {
+MCRT_HD unsigned leg_step(Leg<R>& L, const GridDev& G, Mem& M) {
   constexpr int D = kBlockWalk;
   Ray<R, double>& ry = L.ry;
+  const R kapR = L.kapR;
   WalkBlock<D, R, double> b;
   ray_next_block(ry, b, G, M);
   bool hit = false;
@@ -235,6 +248,51 @@ MCRT_HD unsigned leg_step(Leg<R>& L, const GridDev& G, R kapR, Mem& M) {
 MCRT_HD double forced_depth(const RunParams& P, unsigned slot, unsigned lam, int n, double T) {
   const U4 ws = draw_words(P.seed, stage_package(P, slot, lam), lam, 2u + (unsigned)n);
   return -log1p(u01(ws.x) * expm1(-T));
+}
+
+// Takes package p: its path walk starts (one that misses the grid ends at once).
+template <typename R, int GK, class Mem>
+MCRT_HD void leg_begin(Leg<R>& L, const GridDev& G, Mem& M, const StagePkg& p) {
+  L.slot = p.slot;
+  L.lam = p.lam;
+  L.kapR = (R)M.lam((int)p.lam).kappa;
+  L.mode = kLegPath;
+  L.found = false;
+  L.tau_sR = R(INFINITY);
+  L.comp = R(0);
+  ray_begin<R, GK>(L.ry, G, p.r, p.k);
+}
+
+// The end of a walk of package p's leg after event n: the next walk is set
+// up, or the leg is done and `out` its result (true).
+template <typename R, int GK, class Mem>
+MCRT_HD bool leg_end(Leg<R>& L, const RunParams& P, Mem& M, int n, const StagePkg& p, StageLeg& out) {
+  if (L.mode == kLegPath) {
+    L.T = (double)L.ry.tau;
+    if (L.T == 0.0) {  // nothing to interact with: the package leaves
+      out = StageLeg{0.0, 0.0};
+      return true;
+    }
+    L.tau_s = forced_depth(P, L.slot, L.lam, n, L.T);
+    L.tau_sR = (R)L.tau_s;
+    L.found = false;
+    L.mode = kLegLocate;
+    leg_restart<R, GK>(L, P.G, p.r, p.k);
+    return false;
+  }
+  if (L.found || L.mode == kLegLast) {  // the interaction point
+    double s = L.ry.tin + L.last;
+    if (L.found)
+      s = ray_cell_entry64<R, GK>(L.ry, P.G, p.r, p.k) +
+          (L.tau_s - (double)L.tau_prev) / (M.lam((int)L.lam).kappa * (double)L.rho_hit);
+    out = StageLeg{L.T, s};
+    return true;
+  }
+  L.mode = kLegLast;  // tau_s reached the total by rounding
+  L.tau_sR = R(INFINITY);
+  L.last = 0.0;
+  leg_restart<R, GK>(L, P.G, p.r, p.k);
+  return false;
 }
 
 // ---------------------------------------------------------------------------

@@ -16,7 +16,8 @@ SRC = os.path.join(HERE, "mcrt_emu.cpp")
 CSRC = os.path.join(ROOT, "paper_1410_1629_amd", "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 DEPS = [SRC, os.path.join(INCLUDE, "mcrt.h")] + [os.path.join(CSRC, h) for h in
-                                                ("mcrt_device.hpp", "mcrt_lane.hpp", "mcrt_host.hpp", "mcrt_attached.hpp")]
+                                                ("mcrt_device.hpp", "mcrt_lane.hpp", "mcrt_stage.hpp", "mcrt_host.hpp",
+                                                 "mcrt_attached.hpp")]
 WAVE = 64
 
 
@@ -56,6 +57,8 @@ class Emu:
         lib.emu_set_events_kept.restype = None
         lib.emu_set_chunk_items.argtypes = [C.c_int]
         lib.emu_set_chunk_items.restype = None
+        lib.emu_set_stages.argtypes = [C.c_longlong, C.c_int]
+        lib.emu_set_stages.restype = None
         lib.emu_violation.restype = C.c_char_p
         lib.emu_last_error.restype = C.c_char_p
         self.lib = lib
@@ -107,6 +110,11 @@ class Emu:
     def set_chunk_items(self, n):
         """Packages per adjoint chunk (0: the library's choice)."""
         self.lib.emu_set_chunk_items(int(n))
+
+    def set_stages(self, min_n, orders=12):
+        """Life cycles in stages down to lists of min_n packages and for at
+        most `orders` orders (0: the lane machine alone)."""
+        self.lib.emu_set_stages(int(min_n), int(orders))
 
     def grad(self, prob, adj, wave=WAVE, optics=False, adj_absorbed=None, tape=None, attached=False, **overrides):
         """(dL/drho, stats), or with optics=True (dL/drho, stats, {"albedo",

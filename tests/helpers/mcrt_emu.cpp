@@ -21,6 +21,7 @@
 #include "mcrt_device.hpp"
 #include "mcrt_host.hpp"
 #include "mcrt_lane.hpp"
+#include "mcrt_stage.hpp"
 
 using namespace mcrt;
 
@@ -29,6 +30,8 @@ namespace {
 thread_local std::string g_violation;
 int g_events_kept = 32;  // adjoint event scratch per package, as the library keeps
 int g_chunk_items = 0;   // > 0: smaller adjoint chunks than the library's (tests)
+long long g_stage_min = 0;  // > 0: life cycles that the library may run in stages do, down to lists of this length,
+int g_stage_orders = 12;    // and for at most so many orders
 
 struct Violation : std::runtime_error {
   using std::runtime_error::runtime_error;
@@ -286,6 +289,21 @@ struct HostLifeMem {
   }
 };
 
+// The life-cycle accessor of the lane machine that takes over the packages
+// of a staged list.
+template <typename R, int GK, bool INST>
+struct HostTailMem : HostLifeMem<R, GK, INST> {
+  static constexpr bool kResume = true;
+  std::vector<StagePkg> list;  // the packages to resume, after res_events events
+  int res_events = 0;
+  unsigned long long resume_count() const { return list.size(); }
+  const StagePkg& resume_pkg(unsigned long long i) const {
+    EMU_CHECK(i < list.size(), "resumed package", i, list.size());
+    return list[i];
+  }
+  int resume_events() const { return res_events; }
+};
+
 // The queued peel walk's accessor on regular grids: densities through the
 // life-cycle accessor, cell addresses from the table of per-axis address
 // terms that the peel-ray walk kernel keeps in LDS (lut_entry), every table
@@ -305,6 +323,7 @@ struct HostLutMem {
     }
   }
   R rho(int c) const { return M.rho(c); }
+  const LamDev& lam(int l) const { return M.lam(l); }
   int lut_addr(const int i[3]) const {
     if (lut.empty()) return brick_addr(G, i);
     int c = 0;
@@ -477,6 +496,100 @@ unsigned long long emu_peel_jobs(HostLifeMem<R, GK, INST>& M, const RunParams& P
   return nx;
 }
 
+// A chunk's life cycle in stages, as k_emit, k_leg and k_event run it: lists
+// of packages, each ordered by its position keys and walked by one wavefront
+// of `wave` lanes.  `tail` receives the list that the lane machine takes over.
+template <typename R, int PASS, int GK, bool INST>
+void emu_stages(HostTailMem<R, GK, INST>& tail, const RunParams& P, int orders, int wave, long long cap_steps,
+                StageCounts& c) {
+  HostLifeMem<R, GK, INST>& M = tail;
+  const StageKeys K = stage_keys(P.G);
+  std::vector<StagePkg> list;
+  auto reserve = [&](unsigned mask) {
+    const unsigned long long at = M.job_next;
+    M.job_next += (unsigned)__builtin_popcount(mask);
+    return at;
+  };
+  auto put = [](std::vector<StagePkg>& out, unsigned slot, unsigned lam, const double r[3], const double k[3], double W) {
+    out.push_back(StagePkg{{r[0], r[1], r[2]}, {k[0], k[1], k[2]}, W, slot, lam});
+  };
+  for (unsigned slot = 0; slot < P.n_chunk; ++slot) {
+    unsigned lam = 0;
+    double r[3], k[3], W = 0.0;
+    ++c.n_pk;
+    if (!stage_emit(P, M, slot, lam, r, k, W)) continue;
+    const unsigned mask = stage_frames(P, M, 0, r);
+    stage_peel<R, PASS>(P, M, 0, r, k, W, slot, lam, M.lam((int)lam), mask, reserve(mask), c);
+    put(list, slot, lam, r, k, W);
+  }
+  int n = 0;
+  for (; n < orders && (long long)list.size() >= g_stage_min; ++n) {
+    std::vector<std::pair<unsigned, size_t>> by(list.size());
+    for (size_t q = 0; q < list.size(); ++q) {
+      by[q] = {stage_key(K, list[q].r), q};
+      EMU_CHECK(by[q].first < (1u << kStageKeyBits), "position key", by[q].first, 1 << kStageKeyBits);
+    }
+    std::sort(by.begin(), by.end());
+    std::vector<StagePkg> in(list.size());
+    for (size_t q = 0; q < list.size(); ++q) in[q] = list[by[q].second];
+    // the legs
+    struct LegLane : Leg<R> {
+      bool done = false, busy = false;
+      size_t q = 0;
+    };
+    HostLutMem<R, GK, INST> LM(M, P.G);
+    std::vector<StageLeg> legs(in.size());
+    std::vector<unsigned char> have(in.size(), 0);
+    std::vector<LegLane> lanes(wave);
+    for (auto& L : lanes) leg_init(L);
+    size_t next = 0;
+    run_wave(
+        lanes, P.batch,
+        [&](LegLane& L) {
+          while (!L.ry.active && !L.done) {
+            if (L.busy) {
+              if (!leg_end<R, GK>(L, P, LM, n, in[L.q], legs[L.q])) continue;
+              EMU_CHECK(!have[L.q], "leg ended twice", L.q, in.size());
+              have[L.q] = 1;
+              L.busy = false;
+            }
+            if (next == in.size()) {
+              L.done = true;
+            } else {
+              L.q = next++;
+              L.busy = true;
+              leg_begin<R, GK>(L, P.G, LM, in[L.q]);
+            }
+          }
+        },
+        [&](LegLane& L) {
+          const unsigned x = leg_step(L, P.G, LM);
+          if (L.mode == kLegPath)
+            M.xs[0] += x;
+          else if (L.mode == kLegLocate)
+            M.xs[1] += x;
+        },
+        cap_steps, 0);
+    // the events
+    list.clear();
+    for (size_t q = 0; q < in.size(); ++q) {
+      EMU_CHECK(have[q], "leg read before write", q, in.size());
+      StagePkg& p = in[q];
+      const LamDev& O = M.lam((int)p.lam);
+      if (!stage_move<PASS>(P, M, O, p.slot, n, legs[q].T, legs[q].s, p.r, p.k, p.W, c)) continue;
+      const unsigned mask = stage_frames(P, M, n + 1, p.r);
+      const bool alive = !stage_ends(P, O, n + 1, p.W);
+      if (!alive) c.s_trunc += p.W;
+      stage_peel<R, PASS>(P, M, n + 1, p.r, p.k, p.W, p.slot, p.lam, O, mask, reserve(mask), c);
+      if (!alive) continue;
+      stage_turn(P, O, p.slot, p.lam, n, p.k);
+      put(list, p.slot, p.lam, p.r, p.k, p.W);
+    }
+  }
+  tail.list = list;
+  tail.res_events = n;
+}
+
 template <typename R, bool ADJ, int GK, bool INST>
 int emu_life(const mcrt_grid* grid, const void* rho, const mcrt_optics* optics, int n_src, const mcrt_source* sources,
              int n_det, const mcrt_detector* detectors, const mcrt_opts* opts, double* images, long long n_images,
@@ -521,21 +634,42 @@ int emu_life(const mcrt_grid* grid, const void* rho, const mcrt_optics* optics, 
   const std::vector<R> rho_b = brick_copy(P.G, static_cast<const R*>(rho));
   std::vector<double> abs_b(P.absorbed ? (size_t)P.n_lambda * P.G.ntal : 0, 0.0);
   std::vector<double> grad_b(ADJ && grad ? (size_t)P.G.ncell_pad : 0, 0.0);
-  HostLifeMem<R, GK, INST> M{rho_b.data(), P.G, pr, images, n_images, P.absorbed ? abs_b.data() : nullptr,
-                   (long long)abs_b.size(), adj, n_adj, grad_b.data(), (long long)grad_b.size()};
+  HostTailMem<R, GK, INST> tail{{rho_b.data(), P.G, pr, images, n_images, P.absorbed ? abs_b.data() : nullptr,
+                                 (long long)abs_b.size(), adj, n_adj, grad_b.data(), (long long)grad_b.size()}};
+  HostLifeMem<R, GK, INST>& M = tail;
   P.absorbed = M.absorbed;
   if (images && !ADJ) std::fill(images, images + n_images, 0.0);
   const bool peel = (opts->flags & (MCRT_PEEL_EMIT | MCRT_PEEL_SCAT)) && n_det > 0;
   const long long cap = (long long)P.G.n[0] + P.G.n[1] + P.G.n[2] + 8;
   double sa = 0, se = 0, st = 0;
   // one launch of the life-cycle kernel: fresh lanes, then their statistics
+  bool staged = false;  // set below, once the tape is known
   auto launch = [&](int split) {
     P.split = split;
     M.next = 0;
+    const bool resume = staged && split != 2;
+    if (resume) {
+      StageCounts c;
+      emu_stages<R, ADJ ? kPassA : kPassForward, GK, INST>(tail, P, g_stage_orders, wave, cap, c);
+      sa += c.s_abs;
+      se += c.s_esc;
+      st += c.s_trunc;
+      M.xs[2] += c.x_peel;
+      M.xs[3] += c.n_ev;
+      M.xs[4] += c.n_pk;
+      M.xs[5] += c.n_pl;
+      M.xs[6] += c.n_dep;
+    }
     std::vector<Lane<R>> lanes(wave);
     for (auto& L : lanes) lane_init(L);
     run_wave(
-        lanes, P.batch, [&](Lane<R>& L) { lane_events<R, ADJ>(L, P, M); },
+        lanes, P.batch,
+        [&](Lane<R>& L) {
+          if (resume)
+            lane_events<R, ADJ>(L, P, tail);
+          else
+            lane_events<R, ADJ>(L, P, M);
+        },
         [&](Lane<R>& L) { lane_step<R, ADJ>(L, P, M); },
         cap, 0);
     for (auto& L : lanes) {
@@ -598,6 +732,7 @@ int emu_life(const mcrt_grid* grid, const void* rho, const mcrt_optics* optics, 
     P.ev_k = 1 + P.n_det + (adj_abs ? 1 : 0);
     P.dep_jobs = tape_adj ? 1 : 0;
   }
+  staged = g_stage_min > 0 && !gopt && !adj_abs && !tape_adj && !P.absorbed && opts->peel_queue != -1;
   const size_t per_item = sizeof(double) * ((size_t)P.ev_max * P.ev_k + 1);
   unsigned long long chunk =
       ADJ ? std::min<unsigned long long>(P.n_items, std::max<size_t>(1 << 16, (size_t(1) << 30) / per_item))
@@ -1062,6 +1197,10 @@ extern "C" {
 const char* emu_violation(void) { return g_violation.c_str(); }
 void emu_set_events_kept(int n) { g_events_kept = n; }
 void emu_set_chunk_items(int n) { g_chunk_items = n; }
+void emu_set_stages(long long min_n, int orders) {
+  g_stage_min = min_n;
+  g_stage_orders = orders;
+}
 const char* emu_last_error(void) { return host::last_error().c_str(); }
 
 int emu_run_photons(const mcrt_grid* grid, const void* rho, const mcrt_optics* optics, int n_src,
