@@ -195,7 +195,7 @@ MCRT_HD unsigned leg_step(Leg<R>& L, const GridDev& G, Mem& M) {
         run = t;
       }
     } else {
-      run += dtau;
+      run = d < b.n ? run + dtau : run;  // past the walk's end dtau is 0, or NaN in a cell of infinite density
     }
     n += pos;
     t_run = pos ? b.tend[d] : t_run;

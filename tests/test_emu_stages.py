@@ -88,6 +88,31 @@ def test_all_orders_end_in_the_lane_machine(E, W, kind):
     assert staged[1]["events"] > 12 * born
 
 
+@pytest.mark.parametrize("kind", ["regular", "rect", "tree"])
+def test_opaque_walls_that_absorb_everything(E, W, kind):
+    """Cells of infinite density and albedo 0 (FP64): a leg into one is absorbed whole, also where its walk ends
+    inside a block of crossings.  (With scattered light the walk that starts at such a cell's face has no depth.)"""
+    p = _problem(W, kind, 0, n_pkg=400, albedo=[0.0])
+    rho = np.array(p["rho"], dtype=np.float64)
+    if kind == "tree":
+        rho[::7] = np.inf
+    else:
+        rho = rho.reshape(6, 7, 9)
+        rho[:, :, -1] = rho[0] = np.inf
+    p["rho"] = rho
+    out = []
+    for s in ((0, 0), (1, 12)):
+        E.set_stages(*s)
+        out.append(E.run(p))
+    (img0, _, st0), (img1, _, st1) = out
+    assert np.isfinite(img0).all() and st0["absorbed"] > 0.9 * st0["emitted"]
+    for k in COUNTS:
+        assert st1[k] == st0[k], k
+    for k in ("absorbed", "escaped", "truncated"):
+        assert abs(st1[k] - st0[k]) <= 1e-11 * st0["emitted"], k
+    assert np.abs(img1 - img0).sum() <= 1e-11 * img0.sum()  # the tree's source is walled in: no light
+
+
 @pytest.mark.parametrize("cap", [1, 500])
 def test_a_full_queue_is_walked_by_the_events(E, W, cap):
     """FP64, so the walks in the queue and here agree; which rays they take does not."""
