@@ -17,7 +17,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libmcrt.so")
 SOURCES = [os.path.join(CSRC, "mcrt_kernels.hip")]
 DEPENDS = SOURCES + [os.path.join(CSRC, h) for h in ("mcrt_device.hpp", "mcrt_lane.hpp", "mcrt_host.hpp", "mcrt_attached.hpp",
-                                                      "mcrt_stage.hpp")] + [
+                                                      "mcrt_stage.hpp", "mcrt_blocks.hpp")] + [
     os.path.join(INCLUDE, "mcrt.h")]
 # the memory-system probes the roofline is measured against (not the transport path)
 PROBES_LIB = os.path.join(HERE, "libmcrt_probes.so")

@@ -1,0 +1,99 @@
+// mcrt_blocks.hpp -- which idle device blocks the library keeps between calls,
+// which one a call takes and which have to go.  Host code without HIP calls:
+// the library passes the question whether a block's last use is over in as a
+// function, and frees the blocks that it is handed.  Nothing here allocates or
+// throws, so that blocks can be returned from destructors.
+#pragma once
+
+#include <algorithm>
+#include <cstddef>
+#include <mutex>
+
+namespace mcrt {
+
+constexpr size_t kKeepBytes = size_t(64) << 30, kKeepLarge = size_t(256) << 20;
+constexpr int kKeepBlocks = 16;
+constexpr unsigned long long kKeepCalls = 32;
+
+struct Block {
+  unsigned char* ptr;
+  size_t bytes;
+  int dev;
+  const void* st;  // stream of the last use
+  void* done;      // event: end of the last use
+  unsigned long long use;
+};
+
+class BlockStore {
+ public:
+  // A block of at least `bytes` from the kept ones; false: none fits.
+  // over(block): whether its last use has ended.
+  template <class Over>
+  bool take(size_t bytes, int dev, const void* st, Over over, Block& out) noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    ++clock_;
+    int best = n_;
+    for (int i = 0; i < n_; ++i) {
+      const Block& b = idle_[i];
+      if (b.dev != dev || b.bytes < bytes || b.bytes / 4 > std::max(bytes, size_t(16) << 20)) continue;
+      if (b.st != st && !over(b)) continue;
+      if (best == n_ || b.bytes < idle_[best].bytes) best = i;
+    }
+    if (best == n_) return false;
+    out = remove(best);
+    return true;
+  }
+  // Keeps a block; false: there is no room for it.
+  bool keep(Block b) noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (n_ == kRoom) return false;
+    b.use = clock_;
+    idle_[n_++] = b;
+    return true;
+  }
+  // A block of the device that has to go, the longest unused first; false: none.
+  bool excess(int dev, size_t budget, Block& out) noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    size_t total = 0;
+    int old = n_;
+    for (int i = 0; i < n_; ++i) {
+      if (idle_[i].dev != dev) continue;
+      total += idle_[i].bytes;
+      if (old == n_ || idle_[i].use < idle_[old].use) old = i;
+    }
+    if (old == n_ || (total <= budget && n_ <= kKeepBlocks && idle_[old].use + kKeepCalls >= clock_)) return false;
+    out = remove(old);
+    return true;
+  }
+  // Any block of a device (dev < 0: of all); false: none is left.
+  bool drop(int dev, Block& out) noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (int i = 0; i < n_; ++i)
+      if (dev < 0 || idle_[i].dev == dev) {
+        out = remove(i);
+        return true;
+      }
+    return false;
+  }
+  size_t idle_bytes(int dev) noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    size_t n = 0;
+    for (int i = 0; i < n_; ++i)
+      if (idle_[i].dev == dev) n += idle_[i].bytes;
+    return n;
+  }
+
+ private:
+  Block remove(int i) noexcept {
+    const Block b = idle_[i];
+    for (--n_; i < n_; ++i) idle_[i] = idle_[i + 1];
+    return b;
+  }
+  static constexpr int kRoom = 1024;
+  std::mutex mu_;
+  Block idle_[kRoom];
+  int n_ = 0;
+  unsigned long long clock_ = 0;
+};
+
+}  // namespace mcrt

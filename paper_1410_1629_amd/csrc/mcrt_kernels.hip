@@ -29,6 +29,7 @@
 #include "mcrt.h"
 #include "mcrt_device.hpp"
 #include "mcrt_attached.hpp"
+#include "mcrt_blocks.hpp"
 #include "mcrt_host.hpp"
 #include "mcrt_lane.hpp"
 #include "mcrt_stage.hpp"
@@ -1813,96 +1814,24 @@ int cell_cdf(const double* cell_lum, int nl, int ncell, double* cum, double* til
 // kKeepBlocks) and go back on the stream that replaces them, when 32 calls
 // have not used them, as soon as less than half of the device's memory is
 // free, when an allocation fails, and with mcrt_release_workspaces.
-constexpr size_t kKeepBytes = size_t(64) << 30, kKeepLarge = size_t(256) << 20;
-constexpr size_t kKeepBlocks = 16;
-constexpr unsigned long long kKeepCalls = 32;
-
-struct Block {
-  unsigned char* ptr;
-  size_t bytes;
-  int dev;
-  hipStream_t st;    // of the last use
-  hipEvent_t done;   // end of the last use
-  unsigned long long use;
-};
-
-class BlockStore {
- public:
-  // A block of at least `bytes` from the kept ones; false: none fits.
-  bool take(size_t bytes, int dev, hipStream_t st, Block& out) {
-    std::lock_guard<std::mutex> lock(mu_);
-    ++clock_;
-    size_t best = idle_.size();
-    for (size_t i = 0; i < idle_.size(); ++i) {
-      const Block& b = idle_[i];
-      if (b.dev != dev || b.bytes < bytes || b.bytes / 4 > std::max(bytes, size_t(16) << 20)) continue;
-      if (b.st != st && hipEventQuery(b.done) != hipSuccess) {
-        (void)hipGetLastError();
-        continue;
-      }
-      if (best == idle_.size() || b.bytes < idle_[best].bytes) best = i;
-    }
-    if (best == idle_.size()) return false;
-    out = idle_[best];
-    idle_.erase(idle_.begin() + (long)best);
-    return true;
-  }
-  // Keeps a block (its event recorded), and returns those that have to go.
-  void keep(Block b, size_t budget, std::vector<Block>& out) {
-    std::lock_guard<std::mutex> lock(mu_);
-    b.use = clock_;
-    idle_.push_back(b);
-    for (;;) {  // the longest unused first
-      size_t total = 0, old = idle_.size();
-      for (size_t i = 0; i < idle_.size(); ++i) {
-        if (idle_[i].dev != b.dev) continue;
-        total += idle_[i].bytes;
-        if (old == idle_.size() || idle_[i].use < idle_[old].use) old = i;
-      }
-      if (old == idle_.size() ||
-          (total <= budget && idle_.size() <= kKeepBlocks && idle_[old].use + kKeepCalls >= clock_))
-        return;
-      out.push_back(idle_[old]);
-      idle_.erase(idle_.begin() + (long)old);
-    }
-  }
-  // Removes the idle blocks of a device (dev < 0: of all), smaller ones than
-  // `below` only.
-  void drop(int dev, size_t below, std::vector<Block>& out) {
-    std::lock_guard<std::mutex> lock(mu_);
-    for (size_t i = idle_.size(); i-- > 0;)
-      if ((dev < 0 || idle_[i].dev == dev) && idle_[i].bytes < below) {
-        out.push_back(idle_[i]);
-        idle_.erase(idle_.begin() + (long)i);
-      }
-  }
-  size_t idle_bytes(int dev) {
-    std::lock_guard<std::mutex> lock(mu_);
-    size_t n = 0;
-    for (const Block& b : idle_)
-      if (b.dev == dev) n += b.bytes;
-    return n;
-  }
-
- private:
-  std::mutex mu_;
-  std::vector<Block> idle_;
-  unsigned long long clock_ = 0;
-};
-
 BlockStore& block_store() {
   static BlockStore* const s = new BlockStore;  // not destroyed: the runtime may be gone by then
   return *s;
 }
 
-// Frees blocks on a stream of the current device, after their last use.
-void free_blocks(std::vector<Block>& blocks, hipStream_t st) {
-  for (Block& b : blocks) {
-    (void)hipStreamWaitEvent(st, b.done, 0);
-    (void)hipFreeAsync(b.ptr, st);
-    (void)hipEventDestroy(b.done);
-  }
-  blocks.clear();
+// Frees a block of the current device on a stream, after its last use.
+void free_block(const Block& b, hipStream_t st) {
+  const hipEvent_t done = static_cast<hipEvent_t>(b.done);
+  (void)hipStreamWaitEvent(st, done, 0);
+  (void)hipFreeAsync(b.ptr, st);
+  (void)hipEventDestroy(done);
+}
+
+// Whether a block's last use has ended.
+bool block_over(const Block& b) {
+  if (hipEventQuery(static_cast<hipEvent_t>(b.done)) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
 }
 
 bool stream_capturing(hipStream_t st) {
@@ -1946,34 +1875,35 @@ struct DeviceBlock {
     HIPCHK(hipGetDevice(&dev));
     const bool keep = !stream_capturing(st);
     const RelaxedCapture relaxed;
+    const size_t exact = bytes;
     if (keep) {
-      if (block_store().take(bytes, dev, st, b)) {
+      if (block_store().take(bytes, dev, st, block_over, b)) {
         ptr = b.ptr;
-        HIPCHK(hipStreamWaitEvent(st, b.done, 0));
+        HIPCHK(hipStreamWaitEvent(st, static_cast<hipEvent_t>(b.done), 0));
         return 0;
       }
       const size_t unit = bytes >= kKeepLarge ? size_t(64) << 20 : size_t(1) << 16;  // sizes that vary a little fit
       bytes = (bytes + unit - 1) / unit * unit;
     }
     hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&ptr), bytes, st);
-    if (e != hipSuccess && keep) {  // give the idle blocks back and try again
+    if (e != hipSuccess && keep) {  // give the idle blocks back and ask for no more than the call needs
       (void)hipGetLastError();
-      std::vector<Block> idle;
-      block_store().drop(dev, SIZE_MAX, idle);
-      if (!idle.empty()) {
-        free_blocks(idle, st);
-        HIPCHK(hipStreamSynchronize(st));
-        e = hipMallocAsync(reinterpret_cast<void**>(&ptr), bytes, st);
-      }
+      bytes = exact;
+      Block idle;
+      while (block_store().drop(dev, idle)) free_block(idle, st);
+      HIPCHK(hipStreamSynchronize(st));
+      e = hipMallocAsync(reinterpret_cast<void**>(&ptr), bytes, st);
     }
     if (e != hipSuccess) {
       ptr = nullptr;
       return fail(MCRT_EHIP, "hipMallocAsync of %zu bytes: %s", bytes, hipGetErrorString(e));
     }
-    if (keep && hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess) {
+    hipEvent_t done = nullptr;
+    if (keep && hipEventCreateWithFlags(&done, hipEventDisableTiming) == hipSuccess) {
       b.ptr = ptr;
       b.bytes = bytes;
       b.dev = dev;
+      b.done = done;
     }
     return 0;
   }
@@ -1983,19 +1913,19 @@ struct DeviceBlock {
       (void)hipFreeAsync(ptr, st);
       return;
     }
-    std::vector<Block> gone;
     size_t free_b = 0, total_b = 0;
     b.st = st;
-    if (hipEventRecord(b.done, st) != hipSuccess) {
+    if (hipEventRecord(static_cast<hipEvent_t>(b.done), st) != hipSuccess) {
       (void)hipFreeAsync(ptr, st);
-      (void)hipEventDestroy(b.done);
+      (void)hipEventDestroy(static_cast<hipEvent_t>(b.done));
       return;
     }
     size_t budget = kKeepBytes;
     if (b.bytes >= kKeepLarge && hipMemGetInfo(&free_b, &total_b) == hipSuccess)
       budget = free_b < total_b / 2 ? 0 : std::min(budget, total_b / 4);
-    block_store().keep(b, budget, gone);
-    free_blocks(gone, st);
+    if (!block_store().keep(b)) free_block(b, st);
+    Block gone;
+    while (block_store().excess(b.dev, budget, gone)) free_block(gone, st);
   }
 };
 
@@ -2908,16 +2838,16 @@ int mcrt_release_workspaces(void) {
   try {
     mcrt::host::last_error().clear();
     const RelaxedCapture relaxed;
-    std::vector<Block> idle;
-    block_store().drop(-1, SIZE_MAX, idle);
     int dev = 0;
     HIPCHK(hipGetDevice(&dev));
     hipError_t err = hipSuccess;
-    for (Block& b : idle) {
+    Block b;
+    while (block_store().drop(-1, b)) {
+      const hipEvent_t done = static_cast<hipEvent_t>(b.done);
       hipError_t e = hipSetDevice(b.dev);
-      if (e == hipSuccess) e = hipEventSynchronize(b.done);
+      if (e == hipSuccess) e = hipEventSynchronize(done);
       if (e == hipSuccess) e = hipFree(b.ptr);
-      (void)hipEventDestroy(b.done);
+      (void)hipEventDestroy(done);
       if (e != hipSuccess) err = e;
     }
     HIPCHK(hipSetDevice(dev));
