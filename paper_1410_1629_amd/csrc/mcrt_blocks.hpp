@@ -12,7 +12,7 @@
 namespace mcrt {
 
 constexpr size_t kKeepBytes = size_t(64) << 30, kKeepLarge = size_t(256) << 20;
-constexpr int kKeepBlocks = 16;
+constexpr int kKeepBlocks = 16;  // of one device
 constexpr unsigned long long kKeepCalls = 32;
 
 struct Block {
@@ -55,13 +55,14 @@ class BlockStore {
   bool excess(int dev, size_t budget, Block& out) noexcept {
     std::lock_guard<std::mutex> lock(mu_);
     size_t total = 0;
-    int old = n_;
+    int count = 0, old = n_;
     for (int i = 0; i < n_; ++i) {
       if (idle_[i].dev != dev) continue;
       total += idle_[i].bytes;
+      ++count;
       if (old == n_ || idle_[i].use < idle_[old].use) old = i;
     }
-    if (old == n_ || (total <= budget && n_ <= kKeepBlocks && idle_[old].use + kKeepCalls >= clock_)) return false;
+    if (old == n_ || (total <= budget && count <= kKeepBlocks && idle_[old].use + kKeepCalls >= clock_)) return false;
     out = remove(old);
     return true;
   }

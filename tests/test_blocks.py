@@ -78,6 +78,15 @@ def test_a_device_keeps_so_many_blocks(S):
     assert _gone(S, 0) == [1, 2, 3]
 
 
+def test_each_device_has_blocks_of_its_own(S):
+    """A device that holds its full number of idle blocks leaves the others theirs."""
+    for q in range(1, KEEP_BLOCKS + 1):
+        S.blocks_keep(q, MB, 0, 7)
+    S.blocks_keep(100, 10 * MB, 1, 8)
+    assert _gone(S, 1) == [] and _gone(S, 0) == []
+    assert S.blocks_take(10 * MB, 1, 8) == 100
+
+
 def test_drop_empties_a_device_or_all(S):
     for q, dev in ((1, 0), (2, 1), (3, 0), (4, 2)):
         S.blocks_keep(q, MB, dev, 7)
