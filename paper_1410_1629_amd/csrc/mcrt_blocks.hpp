@@ -13,7 +13,7 @@ namespace mcrt {
 
 constexpr size_t kKeepBytes = size_t(64) << 30, kKeepLarge = size_t(256) << 20;
 constexpr int kKeepBlocks = 16;  // of one device
-constexpr unsigned long long kKeepCalls = 32;
+constexpr unsigned long long kKeepCalls = 32;  // calls of the library, whatever blocks they take
 
 struct Block {
   unsigned char* ptr;
@@ -26,12 +26,16 @@ struct Block {
 
 class BlockStore {
  public:
+  // A call of the library begins.
+  void call() noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    ++clock_;
+  }
   // A block of at least `bytes` from the kept ones; false: none fits.
   // over(block): whether its last use has ended.
   template <class Over>
   bool take(size_t bytes, int dev, const void* st, Over over, Block& out) noexcept {
     std::lock_guard<std::mutex> lock(mu_);
-    ++clock_;
     int best = n_;
     for (int i = 0; i < n_; ++i) {
       const Block& b = idle_[i];

@@ -2476,6 +2476,7 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
   const size_t off_stg = off_aab + (aabs ? align256(sizeof(double) * (size_t)nl * P.G.ncell_pad) : 0);
   const size_t bytes = off_stg + (staged ? StageBytes(chunk).total() : 0);
 
+  block_store().call();
   DeviceBlock blk;
   blk.st = st;
   if (int e = blk.alloc(bytes)) return e;
@@ -2783,6 +2784,7 @@ int trace_impl(const mcrt_grid* grid, const void* rho_dev, double kappa, int pre
   if (fixed) {
     if (int e = scratch_address(&base)) return e;
   } else {
+    block_store().call();
     if (int e = blk.alloc(direct ? off_rho : bytes)) return e;
     base = blk.ptr;
   }
@@ -2960,6 +2962,7 @@ int peel_off(const mcrt_grid* grid, const void* rho_dev, double kappa, double g,
     const size_t bytes = off_rho + (direct ? 0 : (size_t)P.G.ncell_pad * (f32 ? 4 : 8));
     std::vector<unsigned char> blob(off_rho, 0);
     std::memcpy(blob.data(), det.data(), sizeof(DetDev) * det.size());
+    block_store().call();
     DeviceBlock blk;
     blk.st = st;
     if (int e = blk.alloc(bytes)) return e;
@@ -3014,6 +3017,7 @@ int dust_emission(const mcrt_grid* grid, const void* rho_dev, int precision, int
                  off_t = off_b + align256(sizeof(double) * n_lambda),
                  bytes = off_t + align256(sizeof(double) * (kDustTable + 1));
     std::vector<unsigned char> blob(off_t, 0);
+    block_store().call();
     DeviceBlock blk;
     blk.st = st;
     if (int e = blk.alloc(bytes)) return e;

@@ -34,6 +34,7 @@ void blocks_reset(void) {
   g_news = 0;
 }
 unsigned long long blocks_news(void) { return g_news; }
+void blocks_call(void) { g_store->call(); }
 void blocks_set_over(int id, int over) { g_over[id] = over != 0; }
 int blocks_keep(int id, unsigned long long bytes, int dev, int st) {
   Block b{};

@@ -21,7 +21,7 @@ def lib(tmp_path_factory):
                     os.path.join(ROOT, "tests", "helpers", "blocks_emu.cpp"), "-o", so], check=True)
     lib = C.CDLL(so)
     u64, i32 = C.c_ulonglong, C.c_int
-    for name, args, res in (("blocks_reset", [], None), ("blocks_news", [], u64), ("blocks_set_over", [i32, i32], None),
+    for name, args, res in (("blocks_reset", [], None), ("blocks_news", [], u64), ("blocks_set_over", [i32, i32], None), ("blocks_call", [], None),
                             ("blocks_keep", [i32, u64, i32, i32], i32), ("blocks_take", [u64, i32, i32], i32),
                             ("blocks_excess", [i32, u64], i32), ("blocks_drop", [i32], i32),
                             ("blocks_idle_bytes", [i32], u64)):
@@ -64,7 +64,7 @@ def test_a_block_in_use_on_another_stream_is_left(S):
 def test_the_budget_takes_the_longest_unused(S):
     for q in range(1, 5):
         S.blocks_keep(q, 10 * GB, 0, 7)
-        S.blocks_take(1 << 50, 0, 7)
+        S.blocks_call()
     assert _gone(S, 0) == []
     assert _gone(S, 0, 25 * GB) == [1, 2]
     assert S.blocks_idle_bytes(0) == 20 * GB and S.blocks_idle_bytes(1) == 0
@@ -74,8 +74,21 @@ def test_the_budget_takes_the_longest_unused(S):
 def test_a_device_keeps_so_many_blocks(S):
     for q in range(1, KEEP_BLOCKS + 4):
         S.blocks_keep(q, MB, 0, 7)
-        S.blocks_take(1 << 50, 0, 7)
+        S.blocks_call()
     assert _gone(S, 0) == [1, 2, 3]
+
+
+def test_a_block_goes_when_calls_do_not_use_it(S):
+    """Age counts calls, not the blocks they ask for (a run with a peel-ray queue asks for two)."""
+    S.blocks_keep(1, MB, 0, 7)
+    for _ in range(KEEP_CALLS):
+        S.blocks_call()
+        for _ in range(3):
+            S.blocks_take(1 << 50, 0, 7)
+        assert _gone(S, 0) == []
+    S.blocks_call()
+    S.blocks_keep(2, MB, 0, 7)
+    assert _gone(S, 0) == [1]
 
 
 def test_each_device_has_blocks_of_its_own(S):
