@@ -55,8 +55,11 @@ class BlockStore {
     idle_[n_++] = b;
     return true;
   }
-  // A block of the device that has to go, the longest unused first; false: none.
-  bool excess(int dev, size_t budget, Block& out) noexcept {
+  // A block that has to go when device `dev` has kept one: the device's
+  // longest unused, or one of another device that is too old (over(block) says
+  // that nothing has to be waited for there); false: none.
+  template <class Over>
+  bool excess(int dev, size_t budget, Over over, Block& out) noexcept {
     std::lock_guard<std::mutex> lock(mu_);
     size_t total = 0;
     int count = 0, old = n_;
@@ -66,9 +69,16 @@ class BlockStore {
       ++count;
       if (old == n_ || idle_[i].use < idle_[old].use) old = i;
     }
-    if (old == n_ || (total <= budget && count <= kKeepBlocks && idle_[old].use + kKeepCalls >= clock_)) return false;
-    out = remove(old);
-    return true;
+    if (old < n_ && (total > budget || count > kKeepBlocks || aged(idle_[old]))) {
+      out = remove(old);
+      return true;
+    }
+    for (int i = 0; i < n_; ++i)
+      if (idle_[i].dev != dev && aged(idle_[i]) && over(idle_[i])) {
+        out = remove(i);
+        return true;
+      }
+    return false;
   }
   // Any block of a device (dev < 0: of all); false: none is left.
   bool drop(int dev, Block& out) noexcept {
@@ -89,6 +99,7 @@ class BlockStore {
   }
 
  private:
+  bool aged(const Block& b) const noexcept { return b.use + kKeepCalls < clock_; }
   Block remove(int i) noexcept {
     const Block b = idle_[i];
     for (--n_; i < n_; ++i) idle_[i] = idle_[i + 1];

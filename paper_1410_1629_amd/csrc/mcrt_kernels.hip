@@ -1819,12 +1819,28 @@ BlockStore& block_store() {
   return *s;
 }
 
-// Frees a block of the current device on a stream, after its last use.
-void free_block(const Block& b, hipStream_t st) {
+// Frees a block after its last use: one of the current device (`dev`) on a
+// stream of it, one of another device, whose last use is over, on a stream
+// made for it (the pool gives memory back to the device where a stream is
+// waited for; nothing else runs on this one).
+void free_block(const Block& b, int dev, hipStream_t st) {
   const hipEvent_t done = static_cast<hipEvent_t>(b.done);
-  (void)hipStreamWaitEvent(st, done, 0);
-  (void)hipFreeAsync(b.ptr, st);
+  if (b.dev == dev) {
+    (void)hipStreamWaitEvent(st, done, 0);
+    (void)hipFreeAsync(b.ptr, st);
+    (void)hipEventDestroy(done);
+    return;
+  }
+  hipStream_t own = nullptr;
+  if (hipSetDevice(b.dev) == hipSuccess && hipStreamCreateWithFlags(&own, hipStreamNonBlocking) == hipSuccess) {
+    (void)hipFreeAsync(b.ptr, own);
+    (void)hipStreamSynchronize(own);
+    (void)hipStreamDestroy(own);
+  } else {
+    (void)hipFree(b.ptr);
+  }
   (void)hipEventDestroy(done);
+  (void)hipSetDevice(dev);
 }
 
 // Whether a block's last use has ended.
@@ -1890,7 +1906,7 @@ struct DeviceBlock {
       (void)hipGetLastError();
       bytes = exact;
       Block idle;
-      while (block_store().drop(dev, idle)) free_block(idle, st);
+      while (block_store().drop(dev, idle)) free_block(idle, dev, st);
       HIPCHK(hipStreamSynchronize(st));
       e = hipMallocAsync(reinterpret_cast<void**>(&ptr), bytes, st);
     }
@@ -1923,9 +1939,10 @@ struct DeviceBlock {
     size_t budget = kKeepBytes;
     if (b.bytes >= kKeepLarge && hipMemGetInfo(&free_b, &total_b) == hipSuccess)
       budget = free_b < total_b / 2 ? 0 : std::min(budget, total_b / 4);
-    if (!block_store().keep(b)) free_block(b, st);
+    const RelaxedCapture relaxed;
+    if (!block_store().keep(b)) free_block(b, b.dev, st);
     Block gone;
-    while (block_store().excess(b.dev, budget, gone)) free_block(gone, st);
+    while (block_store().excess(b.dev, budget, block_over, gone)) free_block(gone, b.dev, st);
   }
 };
 

@@ -15,6 +15,7 @@ bool g_over[4096];  // by block number: its last use has ended
 
 const void* stream(int s) { return reinterpret_cast<const void*>((size_t)s); }
 int number(const Block& b) { return (int)reinterpret_cast<size_t>(b.ptr); }
+bool over(const Block& b) { return g_over[number(b)]; }
 }  // namespace
 
 void* operator new(size_t n) {
@@ -46,11 +47,11 @@ int blocks_keep(int id, unsigned long long bytes, int dev, int st) {
 }
 int blocks_take(unsigned long long bytes, int dev, int st) {
   Block b;
-  return g_store->take(bytes, dev, stream(st), [](const Block& q) { return g_over[number(q)]; }, b) ? number(b) : 0;
+  return g_store->take(bytes, dev, stream(st), over, b) ? number(b) : 0;
 }
 int blocks_excess(int dev, unsigned long long budget) {
   Block b;
-  return g_store->excess(dev, budget, b) ? number(b) : 0;
+  return g_store->excess(dev, budget, over, b) ? number(b) : 0;
 }
 int blocks_drop(int dev) {
   Block b;

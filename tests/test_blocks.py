@@ -91,6 +91,22 @@ def test_a_block_goes_when_calls_do_not_use_it(S):
     assert _gone(S, 0) == [1]
 
 
+def test_a_device_that_is_no_longer_used_gives_its_blocks_back(S):
+    """Calls on one device let the blocks of another grow old too; one whose last use goes on is left for later."""
+    S.blocks_keep(1, GB, 0, 7)
+    S.blocks_keep(2, GB, 0, 7)
+    S.blocks_set_over(2, 0)
+    for _ in range(KEEP_CALLS):
+        S.blocks_call()
+    S.blocks_keep(3, GB, 1, 8)
+    assert _gone(S, 1) == []
+    S.blocks_call()
+    S.blocks_keep(4, GB, 1, 8)
+    assert _gone(S, 1) == [1]
+    S.blocks_set_over(2, 1)
+    assert _gone(S, 1) == [2] and S.blocks_idle_bytes(1) == 2 * GB
+
+
 def test_each_device_has_blocks_of_its_own(S):
     """A device that holds its full number of idle blocks leaves the others theirs."""
     for q in range(1, KEEP_BLOCKS + 1):
