@@ -15,6 +15,12 @@ constexpr size_t kKeepBytes = size_t(64) << 30, kKeepLarge = size_t(256) << 20;
 constexpr int kKeepBlocks = 16;  // of one device
 constexpr unsigned long long kKeepCalls = 32;  // calls of the library, whatever blocks they take
 
+// What a device with `total_b` bytes, `free_b` of them free beside the idle
+// blocks, may keep.
+inline size_t keep_budget(size_t free_b, size_t total_b) {
+  return free_b < total_b / 2 ? 0 : std::min(kKeepBytes, total_b / 4);
+}
+
 struct Block {
   unsigned char* ptr;
   size_t bytes;

@@ -1929,18 +1929,19 @@ struct DeviceBlock {
       (void)hipFreeAsync(ptr, st);
       return;
     }
-    size_t free_b = 0, total_b = 0;
     b.st = st;
     if (hipEventRecord(static_cast<hipEvent_t>(b.done), st) != hipSuccess) {
       (void)hipFreeAsync(ptr, st);
       (void)hipEventDestroy(static_cast<hipEvent_t>(b.done));
       return;
     }
-    size_t budget = kKeepBytes;
-    if (b.bytes >= kKeepLarge && hipMemGetInfo(&free_b, &total_b) == hipSuccess)
-      budget = free_b < total_b / 2 ? 0 : std::min(budget, total_b / 4);
     const RelaxedCapture relaxed;
     if (!block_store().keep(b)) free_block(b, b.dev, st);
+    // Every call looks at the device's memory once its idle blocks are worth
+    // the 4.5 us that takes (a call of few rays lasts 80 us).
+    size_t free_b = 0, total_b = 0, budget = kKeepBytes;
+    if (block_store().idle_bytes(b.dev) >= kKeepLarge && hipMemGetInfo(&free_b, &total_b) == hipSuccess)
+      budget = keep_budget(free_b, total_b);
     Block gone;
     while (block_store().excess(b.dev, budget, block_over, gone)) free_block(gone, b.dev, st);
   }

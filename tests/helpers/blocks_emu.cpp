@@ -57,6 +57,9 @@ int blocks_drop(int dev) {
   Block b;
   return g_store->drop(dev, b) ? number(b) : 0;
 }
+unsigned long long blocks_budget(unsigned long long free_b, unsigned long long total_b) {
+  return keep_budget(free_b, total_b);
+}
 unsigned long long blocks_idle_bytes(int dev) { return g_store->idle_bytes(dev); }
 
 }  // extern "C"

@@ -24,7 +24,7 @@ def lib(tmp_path_factory):
     for name, args, res in (("blocks_reset", [], None), ("blocks_news", [], u64), ("blocks_set_over", [i32, i32], None), ("blocks_call", [], None),
                             ("blocks_keep", [i32, u64, i32, i32], i32), ("blocks_take", [u64, i32, i32], i32),
                             ("blocks_excess", [i32, u64], i32), ("blocks_drop", [i32], i32),
-                            ("blocks_idle_bytes", [i32], u64)):
+                            ("blocks_idle_bytes", [i32], u64), ("blocks_budget", [u64, u64], u64)):
         getattr(lib, name).argtypes, getattr(lib, name).restype = args, res
     return lib
 
@@ -69,6 +69,13 @@ def test_the_budget_takes_the_longest_unused(S):
     assert _gone(S, 0, 25 * GB) == [1, 2]
     assert S.blocks_idle_bytes(0) == 20 * GB and S.blocks_idle_bytes(1) == 0
     assert _gone(S, 0, 0) == [3, 4]
+
+
+def test_what_a_device_may_keep(S):
+    assert S.blocks_budget(200 * GB, 288 * GB) == 64 * GB  # 64 GiB
+    assert S.blocks_budget(60 * GB, 64 * GB) == 16 * GB    # or a quarter of the device
+    assert S.blocks_budget(144 * GB, 288 * GB) == 64 * GB
+    assert S.blocks_budget(144 * GB - 1, 288 * GB) == 0    # nothing with less than half of it free
 
 
 def test_a_device_keeps_so_many_blocks(S):
