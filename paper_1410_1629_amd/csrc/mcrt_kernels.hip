@@ -1871,14 +1871,14 @@ struct RelaxedCapture {
   RelaxedCapture& operator=(const RelaxedCapture&) = delete;
 };
 
-// The device's free memory, counting the idle blocks (a call may take them
-// or give them back).
-int free_memory(size_t* free_b) {
+// The device's free memory, counting the idle blocks where the call may take
+// them or give them back: not where its stream is being recorded.
+int free_memory(hipStream_t st, size_t* free_b) {
   size_t total_b = 0;
   int dev = 0;
   HIPCHK(hipMemGetInfo(free_b, &total_b));
   HIPCHK(hipGetDevice(&dev));
-  *free_b += block_store().idle_bytes(dev);
+  if (!stream_capturing(st)) *free_b += block_store().idle_bytes(dev);
   return 0;
 }
 
@@ -2021,7 +2021,7 @@ int make_peel_queue(const mcrt_opts& o, const host::Prepared& pr, unsigned long 
     cap = chunk * (unsigned long long)pr.P.n_det * 8ull;
     cap = std::min(std::max(cap, 1ull << 16), 1ull << 31);
     size_t free_b = 0;
-    if (int e = free_memory(&free_b)) return e;
+    if (int e = free_memory(st, &free_b)) return e;
     cap = std::min<unsigned long long>(cap, free_b / 4 / kQueueBytesPerRay);
     if (cap == 0) return 0;
   }
@@ -2446,7 +2446,7 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
   const bool queued = peel && opts->peel_queue != -1;  // the attached gradient queues its deposit walks only
   P.depth_drop = adjoint ? kDepthDropAdjoint : 0;
   size_t free_b = 0;
-  if (int e = free_memory(&free_b)) return e;
+  if (int e = free_memory(st, &free_b)) return e;
   unsigned long long most = P.n_items;
   if (adjoint)
     most = std::min<unsigned long long>(most, std::max<size_t>(1 << 16, std::min(kScratchBytes, free_b / 4) / per_item));

@@ -65,3 +65,44 @@ def test_memory_goes_when_the_device_fills():
     torch.cuda.empty_cache()
     assert now > torch.cuda.mem_get_info()[1] // 2 - (8 << 30) + LARGE
     assert _free() > before - LARGE // 2
+
+
+def test_a_recorded_run_plans_without_the_kept_memory():
+    """A run that is recorded into a graph cannot take kept blocks or give them back: its chunks are those that the
+    memory beside them allows.  (Nothing of the graphs is run.)"""
+    import ctypes as C
+    import torch
+    from paper_1410_1629_amd import binding as B
+    from paper_1410_1629_amd import workloads as W
+    hip = C.CDLL("libamdhip64.so")
+    stream = torch.cuda.Stream()
+    p = W.cube(n_packages=30_000_000, precision=1)
+    p["flags"] = 3
+    rho = B.density_tensor(p)
+    images = torch.empty(B.image_shape(p), dtype=torch.float64, device="cuda")
+
+    def nodes():
+        graph, n = C.c_void_p(), C.c_size_t(0)
+        assert hip.hipStreamBeginCapture(C.c_void_p(stream.cuda_stream), 0) == 0
+        try:
+            B.run_photons(p, rho, images, stats=False, stream=stream)
+        finally:
+            ended = hip.hipStreamEndCapture(C.c_void_p(stream.cuda_stream), C.byref(graph))
+        assert ended == 0 and hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+        assert hip.hipGraphDestroy(graph) == 0
+        return n.value
+
+    nodes()  # what a first recording sets up
+    B.run_photons(dict(p, n_packages=1000), rho, images, stats=False, peel_queue=(24 << 30) // 74)
+    free = _free()
+    held = torch.empty(free - (24 << 30), dtype=torch.uint8, device="cuda")  # 24 GiB free, about as much kept
+    beside = nodes()
+    B.release_workspaces()
+    more = torch.empty(_free() - (24 << 30), dtype=torch.uint8, device="cuda")
+    assert more.numel() > 20 << 30
+    alone = nodes()
+    del held, more
+    torch.cuda.empty_cache()
+    assert beside == alone
+    B.release_workspaces()
+    assert nodes() < alone  # with all memory free the run takes fewer chunks
