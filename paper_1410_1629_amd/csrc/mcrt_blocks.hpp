@@ -21,11 +21,19 @@ inline size_t keep_budget(size_t free_b, size_t total_b) {
   return free_b < total_b / 2 ? 0 : std::min(kKeepBytes, total_b / 4);
 }
 
+// What tells streams apart.  The handle of the stream that every thread has
+// of its own (per_thread) is the same in all of them: there the thread itself
+// does.
+inline const void* stream_key(const void* st, const void* per_thread) noexcept {
+  static thread_local const char own = 0;
+  return st == per_thread ? static_cast<const void*>(&own) : st;
+}
+
 struct Block {
   unsigned char* ptr;
   size_t bytes;
   int dev;
-  const void* st;  // stream of the last use
+  const void* st;  // stream of the last use (stream_key)
   void* done;      // event: end of the last use
   unsigned long long use;
 };

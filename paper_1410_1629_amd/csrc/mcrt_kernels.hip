@@ -1893,7 +1893,7 @@ struct DeviceBlock {
     const RelaxedCapture relaxed;
     const size_t exact = bytes;
     if (keep) {
-      if (block_store().take(bytes, dev, st, block_over, b)) {
+      if (block_store().take(bytes, dev, stream_key(st, hipStreamPerThread), block_over, b)) {
         ptr = b.ptr;
         HIPCHK(hipStreamWaitEvent(st, static_cast<hipEvent_t>(b.done), 0));
         return 0;
@@ -1929,7 +1929,7 @@ struct DeviceBlock {
       (void)hipFreeAsync(ptr, st);
       return;
     }
-    b.st = st;
+    b.st = stream_key(st, hipStreamPerThread);
     if (hipEventRecord(static_cast<hipEvent_t>(b.done), st) != hipSuccess) {
       (void)hipFreeAsync(ptr, st);
       (void)hipEventDestroy(static_cast<hipEvent_t>(b.done));

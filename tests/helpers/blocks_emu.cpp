@@ -13,7 +13,10 @@ unsigned long long g_news = 0;
 BlockStore* g_store = nullptr;
 bool g_over[4096];  // by block number: its last use has ended
 
-const void* stream(int s) { return reinterpret_cast<const void*>((size_t)s); }
+constexpr size_t kPerThread = 2;  // the stream that every thread has of its own
+const void* stream(int s) {
+  return stream_key(reinterpret_cast<const void*>((size_t)s), reinterpret_cast<const void*>(kPerThread));
+}
 int number(const Block& b) { return (int)reinterpret_cast<size_t>(b.ptr); }
 bool over(const Block& b) { return g_over[number(b)]; }
 }  // namespace

@@ -4,6 +4,7 @@ happens in destructors).  Blocks are numbers, streams and devices too."""
 import ctypes as C
 import os
 import subprocess
+import threading
 
 import pytest
 
@@ -59,6 +60,18 @@ def test_a_block_in_use_on_another_stream_is_left(S):
     S.blocks_set_over(1, 0)
     assert S.blocks_take(90 * MB, 0, 8) == 0
     assert S.blocks_take(90 * MB, 0, 7) == 1  # its own stream waits for it by order
+
+
+def test_the_per_thread_stream_is_another_in_each_thread(S):
+    """Its handle (2) is the same everywhere; calls of two threads on it must not wait for one another."""
+    S.blocks_keep(1, 100 * MB, 0, 2)
+    S.blocks_set_over(1, 0)
+    got = []
+    t = threading.Thread(target=lambda: got.append(S.blocks_take(90 * MB, 0, 2)))
+    t.start()
+    t.join()
+    assert got == [0]
+    assert S.blocks_take(90 * MB, 0, 2) == 1
 
 
 def test_the_budget_takes_the_longest_unused(S):
