@@ -500,10 +500,11 @@ int mcrt_release_workspaces(void);
 /* Message for the last nonzero return on the calling thread ("" if none). */
 const char *mcrt_last_error(void);
 
-/* ABI version of this header. */
+/* ABI version of this header: another one for every change of its structs
+ * and of the set of its functions. */
 int mcrt_abi_version(void);
 
-#define MCRT_ABI_VERSION 18
+#define MCRT_ABI_VERSION 19
 
 #ifdef __cplusplus
 }

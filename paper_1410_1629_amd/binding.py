@@ -89,7 +89,7 @@ class Stats(C.Structure):
 _lib = None
 
 # Exported symbols of include/mcrt.h.
-ABI_VERSION = 18  # MCRT_ABI_VERSION of the header these structs follow
+ABI_VERSION = 19  # MCRT_ABI_VERSION of the header these structs follow
 SYMBOLS = ("run_photons", "trace_path", "trace_path_noalloc", "peel_off", "backward_density", "backward",
            "dust_emission", "mcrt_release_workspaces", "mcrt_tape_bytes", "mcrt_last_error", "mcrt_abi_version")
 NOALLOC_SCRATCH_BYTES = 96 << 20  # MCRT_NOALLOC_SCRATCH_BYTES
@@ -108,6 +108,12 @@ def load():
     # first HIP call found no device)
     import torch  # noqa: F401
     lib = C.CDLL(LIB_PATH)
+    # before any other symbol is looked up: another version may lack it
+    lib.mcrt_abi_version.argtypes = []
+    lib.mcrt_abi_version.restype = C.c_int
+    if lib.mcrt_abi_version() != ABI_VERSION:
+        raise RuntimeError("libmcrt.so has ABI version %d, the binding expects %d; rebuild it" % (
+            lib.mcrt_abi_version(), ABI_VERSION))
     P, i32, i64, d = C.c_void_p, C.c_int32, C.c_int64, C.c_double
     lib.run_photons.argtypes = [C.POINTER(Grid), P, C.POINTER(Optics), C.c_int, C.POINTER(Source), C.c_int,
                                 C.POINTER(Detector), C.POINTER(Opts), P, P, C.POINTER(Stats), P]
@@ -134,11 +140,6 @@ def load():
     lib.mcrt_last_error.restype = C.c_char_p
     lib.mcrt_tape_bytes.argtypes = [C.POINTER(Optics), C.c_int, C.POINTER(Opts)]
     lib.mcrt_tape_bytes.restype = C.c_uint64
-    lib.mcrt_abi_version.argtypes = []
-    lib.mcrt_abi_version.restype = C.c_int
-    if lib.mcrt_abi_version() != ABI_VERSION:
-        raise RuntimeError("libmcrt.so has ABI version %d, the binding expects %d; rebuild it" % (
-            lib.mcrt_abi_version(), ABI_VERSION))
     _lib = lib
     return lib
 
