@@ -2970,8 +2970,11 @@ int peel_off(const mcrt_grid* grid, const void* rho_dev, double kappa, double g,
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     PeelParams P;
     std::memset(&P, 0, sizeof P);
+    // a grid whose bricks are too many is refused on either walk
+    if (int e = host::make_grid(*grid, host::elem_bytes(precision), 0, P.G)) return e;
     const bool direct = walk_direct(*grid, n_events * n_det);
-    if (int e = host::make_grid(*grid, host::elem_bytes(precision), direct ? kRowMajor : 0, P.G)) return e;
+    if (direct)
+      if (int e = host::make_grid(*grid, host::elem_bytes(precision), kRowMajor, P.G)) return e;
     const bool f32 = precision == MCRT_PREC_FP32;
     std::vector<DetDev> det = host::make_dets(n_det, detectors, nullptr);
     const size_t off_cnt = align256(sizeof(DetDev) * det.size());
