@@ -497,6 +497,11 @@ int dust_emission(const mcrt_grid *grid, const void *rho_dev, int precision, int
  * every device; waits for the calls that used it).  Returns 0 or MCRT_EHIP. */
 int mcrt_release_workspaces(void);
 
+/* Bytes of device memory that the library keeps idle on the current device:
+ * a program that asks the device for its free memory may add them (calls use
+ * them, and mcrt_release_workspaces gives them back). */
+uint64_t mcrt_kept_bytes(void);
+
 /* Message for the last nonzero return on the calling thread ("" if none). */
 const char *mcrt_last_error(void);
 
@@ -504,7 +509,7 @@ const char *mcrt_last_error(void);
  * and of the set of its functions. */
 int mcrt_abi_version(void);
 
-#define MCRT_ABI_VERSION 19
+#define MCRT_ABI_VERSION 20
 
 #ifdef __cplusplus
 }

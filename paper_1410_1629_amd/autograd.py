@@ -7,7 +7,8 @@ which replays every package from its random numbers and accumulates the
 detached (score-function) derivative of the images -- the derivative of the
 reweighted estimator whose paths are held fixed.  Both run entirely in the
 HIP kernels.  When the run can keep an adjoint tape (binding.tape_bytes)
-and it fits in a quarter of the free device memory, the forward run fills
+and it fits in a quarter of the free device memory (what torch and the
+library keep idle counts as free, so every step decides alike), the forward run fills
 one and the backward pass reads T and the peel-off contributions from it,
 replaying each package once instead of twice (prob["adjoint_tape"] = False
 turns this off).  prob["adjoint_estimator"] = "attached" makes RTImage's
@@ -37,8 +38,17 @@ def _tape_for(prob, device):
     n = binding.tape_bytes(prob)
     if n == 0:
         return None
-    free, _ = torch.cuda.mem_get_info(device)
-    return torch.empty(n, dtype=torch.uint8, device=device) if n < free // 4 else None
+    with torch.cuda.device(device):
+        free, _ = torch.cuda.mem_get_info()
+        cached = torch.cuda.memory_reserved() - torch.cuda.memory_allocated()
+        if n >= (free + cached + binding.kept_bytes()) // 4:
+            return None
+        if n > free + cached:  # part of it is what the library keeps
+            binding.release_workspaces()
+        try:
+            return torch.empty(n, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:  # torch's idle memory is in pieces
+            return None
 
 
 class RTImage(torch.autograd.Function):

@@ -89,9 +89,9 @@ class Stats(C.Structure):
 _lib = None
 
 # Exported symbols of include/mcrt.h.
-ABI_VERSION = 19  # MCRT_ABI_VERSION of the header these structs follow
+ABI_VERSION = 20  # MCRT_ABI_VERSION of the header these structs follow
 SYMBOLS = ("run_photons", "trace_path", "trace_path_noalloc", "peel_off", "backward_density", "backward",
-           "dust_emission", "mcrt_release_workspaces", "mcrt_tape_bytes", "mcrt_last_error", "mcrt_abi_version")
+           "dust_emission", "mcrt_release_workspaces", "mcrt_kept_bytes", "mcrt_tape_bytes", "mcrt_last_error", "mcrt_abi_version")
 NOALLOC_SCRATCH_BYTES = 96 << 20  # MCRT_NOALLOC_SCRATCH_BYTES
 
 
@@ -136,6 +136,8 @@ def load():
     lib.dust_emission.restype = C.c_int
     lib.mcrt_release_workspaces.argtypes = []
     lib.mcrt_release_workspaces.restype = C.c_int
+    lib.mcrt_kept_bytes.argtypes = []
+    lib.mcrt_kept_bytes.restype = C.c_uint64
     lib.mcrt_last_error.argtypes = []
     lib.mcrt_last_error.restype = C.c_char_p
     lib.mcrt_tape_bytes.argtypes = [C.POINTER(Optics), C.c_int, C.POINTER(Opts)]
@@ -180,6 +182,12 @@ def release_workspaces():
     """mcrt_release_workspaces: gives back the device memory that the library
     keeps between calls."""
     _check(load().mcrt_release_workspaces())
+
+
+def kept_bytes():
+    """mcrt_kept_bytes: the idle device memory that the library keeps on the
+    current device."""
+    return int(load().mcrt_kept_bytes())
 
 
 def _ptr(t):

@@ -2878,6 +2878,15 @@ int mcrt_release_workspaces(void) {
   }
 }
 
+uint64_t mcrt_kept_bytes(void) {
+  int dev = 0;
+  try {
+    return hipGetDevice(&dev) == hipSuccess ? block_store().idle_bytes(dev) : 0;
+  } catch (...) {
+    return 0;
+  }
+}
+
 const char* mcrt_last_error(void) { return mcrt::host::last_error().c_str(); }
 
 int run_photons(const mcrt_grid* grid, const void* rho_dev, const mcrt_optics* optics, int n_src,

@@ -11,14 +11,14 @@ from paper_1410_1629_amd import binding as B
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 V18 = {"run_photons", "trace_path", "trace_path_noalloc", "peel_off", "backward_density", "backward", "dust_emission",
        "mcrt_tape_bytes", "mcrt_last_error", "mcrt_abi_version"}
-CALLS = {18: V18, 19: V18 | {"mcrt_release_workspaces"}}
+CALLS = {18: V18, 19: V18 | {"mcrt_release_workspaces"}, 20: V18 | {"mcrt_release_workspaces", "mcrt_kept_bytes"}}
 
 
 def test_the_version_names_the_exported_calls():
     assert CALLS[B.ABI_VERSION] == set(B.SYMBOLS)
 
 
-@pytest.mark.parametrize("version", [18, B.ABI_VERSION + 1])
+@pytest.mark.parametrize("version", [18, 19, B.ABI_VERSION + 1])
 def test_a_library_of_another_version_is_refused_by_its_version(tmp_path, monkeypatch, version):
     src, lib = tmp_path / "old.c", tmp_path / "libmcrt.so"
     src.write_text("int mcrt_abi_version(void) { return %d; }\n" % version +
