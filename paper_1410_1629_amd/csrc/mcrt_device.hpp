@@ -485,14 +485,17 @@ struct DustDev {
 
 MCRT_HD double dust_step() { return log(kDustTmax) / kDustTable; }
 
-// e^u - 1 for 0 <= u < 700, within 1.6 units of 2^-53: u = n ln 2 + r with |r|
+// e^u - 1 for 0 <= u < 700, within 1.6 units of 2^-53 of it: u = n ln 2 + r with |r|
 // <= ln 2 / 2, e^r - 1 = r + w by its Taylor series up to r^14 / 14! (below
 // 1e-17 of it), and 2^n (r + w) + (2^n - 1) with the first sum's remainder.
+// ln 2 = kLn2 + kLn2Rest: kLn2 is ln 2 rounded to 43 binary places, so that n
+// kLn2 is exact for n < 2^10 (53 bits), and the rest is rounded to a double.
+constexpr double kLn2 = 0x1.62e42fefa38p-1, kLn2Rest = 0x1.ef35793c7673p-45;
 MCRT_HD double expm1_pos(double u) {
   const double n = rint(u * 1.4426950408889634);
-  const double v = fma(n, -6.93147180369123816490e-01, u);  // ln 2 in two parts
-  const double r = fma(n, -1.9082149292705877e-10, v);
-  const double low = fma(n, -1.9082149292705877e-10, v - r);
+  const double v = fma(n, -kLn2, u);
+  const double r = fma(n, -kLn2Rest, v);
+  const double low = fma(n, -kLn2Rest, v - r);
   double q = 1.0 / 87178291200.0;  // 1 / 14!
   constexpr double f[] = {1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0,
                           1.0 / 40320.0,      1.0 / 5040.0,      1.0 / 720.0,      1.0 / 120.0,     1.0 / 24.0,
@@ -505,8 +508,8 @@ MCRT_HD double expm1_pos(double u) {
   return h + fma(s, w, fma(s, r, c - h));
 }
 
-// a / d for normal d, rounded once (a reciprocal by Newton's method, then a
-// correction by the remainder): on the device a third of the instructions
+// a / d for normal d, to within an ulp (a reciprocal by Newton's method, then
+// a correction by the remainder): on the device a third of the instructions
 // of a division, which also handles what cannot occur here.  `inv` receives
 // 1 / d to within an ulp.
 MCRT_HD double div_normal(double a, double d, double& inv) {
@@ -525,7 +528,7 @@ MCRT_HD double div_normal(double a, double d, double& inv) {
 
 // One wavelength's a / (exp(b / T) - 1), with u = b / T and 1 / (exp(u) - 1);
 // invT = 1 / T.  (A relative error e of u is one of u e in the result, so u is
-// rounded once too.)  Factors that could leave the normal range take the
+// corrected by its remainder too.)  Factors that could leave the normal range take the
 // plain functions.
 MCRT_HD double dust_term(double a, double b, double T, double invT, double& u, double& inv) {
   u = b * invT;

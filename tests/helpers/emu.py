@@ -57,6 +57,8 @@ class Emu:
         lib.emu_set_events_kept.restype = None
         lib.emu_set_chunk_items.argtypes = [C.c_int]
         lib.emu_set_chunk_items.restype = None
+        lib.emu_expm1.argtypes = [C.c_int, P, P]
+        lib.emu_expm1.restype = None
         lib.emu_set_stages.argtypes = [C.c_longlong, C.c_int]
         lib.emu_set_stages.restype = None
         lib.emu_violation.restype = C.c_char_p
@@ -110,6 +112,13 @@ class Emu:
     def set_chunk_items(self, n):
         """Packages per adjoint chunk (0: the library's choice)."""
         self.lib.emu_set_chunk_items(int(n))
+
+    def expm1(self, u):
+        """The dust emission's e^u - 1 (0 <= u < 700)."""
+        u = np.ascontiguousarray(u, dtype=np.float64)
+        out = np.empty_like(u)
+        self.lib.emu_expm1(u.size, self._p(u), self._p(out))
+        return out
 
     def set_stages(self, min_n, orders=12):
         """Life cycles in stages down to lists of min_n packages and for at

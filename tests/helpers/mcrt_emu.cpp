@@ -1201,6 +1201,9 @@ void emu_set_stages(long long min_n, int orders) {
   g_stage_min = min_n;
   g_stage_orders = orders;
 }
+void emu_expm1(int n, const double* u, double* out) {
+  for (int i = 0; i < n; ++i) out[i] = expm1_pos(u[i]);
+}
 const char* emu_last_error(void) { return host::last_error().c_str(); }
 
 int emu_run_photons(const mcrt_grid* grid, const void* rho, const mcrt_optics* optics, int n_src,
