@@ -67,9 +67,21 @@ BYTES_PER_DEPOSIT = 8
 BYTES_PER_PIXEL = 8
 BYTES_PER_RAY = 56
 COPY_BYTES = 1 << 30
+# A forward run without an absorbed tally, in chunks of at least this many
+# packages, runs its life cycle in stages: per chunk one emission, then per
+# scattering order an ordering of the packages, their legs and their events, and
+# the lane machine for what is left.
+STAGE_ITEMS = 1 << 20
 # kernels as rocprofv3 names them (FP32 path, regular grid, frames only; the
-# peel-ray walk with its LDS table of address terms)
+# leg and peel-ray walks with their LDS table of address terms)
 KERNELS = {
+    "emit": "void mcrt::k_emit<float, 0, false, 0>(mcrt::StageParams)",
+    "count": "mcrt::k_count(unsigned int const*, unsigned long long const*, unsigned int*, unsigned long long)",
+    "move": "mcrt::k_move(mcrt::StagePkg const*, unsigned int const*, unsigned long long const*, unsigned int const*, "
+            "mcrt::StagePkg*, unsigned long long)",
+    "leg": "void mcrt::k_leg<float, 0, true>(mcrt::StageParams)",
+    "event": "void mcrt::k_event<float, 0, false, 0>(mcrt::StageParams)",
+    "tail": "void mcrt::k_tail<float, false, 0, false>(mcrt::RunParams, mcrt::StageTail)",
     "life_forward": "void mcrt::k_life<float, false, 0, false>(mcrt::RunParams)",
     "peel_tau_forward": "void mcrt::k_peeltau<float, false, 0, false, true>(mcrt::PeelJobParams)",
     "life_adjoint": "void mcrt::k_life<float, true, 0, false>(mcrt::RunParams)",
@@ -78,6 +90,8 @@ KERNELS = {
     "trace": "void mcrt::k_trace<float, 0, 4>(mcrt::TraceParams)",
     "attached": "void mcrt::k_attached<float, 0, 2>(mcrt::RunParams)",
 }
+# the kernels of the stages; the first one is launched once per chunk
+STAGES = ("emit", "count", "move", "leg", "event", "tail")
 # the attached gradient's workspace: 11 FP64 values per event, written in the
 # forward sweep and read back in the reverse sweep
 BYTES_PER_ATTACHED_EVENT = 2 * 11 * 8
@@ -97,7 +111,8 @@ def source_hash():
 def traffic_for(workload, key):
     """Hardware bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated) of a
     kernel on a workload from the committed counter summary, if it was
-    taken on the current kernel source; else None."""
+    taken on the current kernel source; else None.  For the stages
+    ("stages_forward") the bytes of all their kernels per chunk."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -108,7 +123,13 @@ def traffic_for(workload, key):
         return None
     if rec.get("source_hash") != source_hash():
         return None
-    k = rec.get("workloads", {}).get(workload, {}).get(key)
+    w = rec.get("workloads", {}).get(workload, {})
+    if key == "stages_forward":
+        parts = [w.get(k) for k in STAGES]
+        if not all(parts):
+            return None
+        return sum(p["bytes_per_launch"] * p["dispatches"] for p in parts) / parts[0]["dispatches"]
+    k = w.get(key)
     return k.get("bytes_per_launch") if k else None
 
 
@@ -133,17 +154,37 @@ def kernel_work(st, prec, adjoint):
     return out
 
 
-def rooflines(st, prec, adjoint, workload, step_ms, level):
-    """Roofline records of every kernel of a call (per launch)."""
+def in_stages(st, adjoint, tally):
+    """Whether a call with these statistics ran its life cycle in stages: a
+    forward run without a tally, or the first of the two replays of an adjoint
+    that has no tape (and so walks its peel rays: peel_ms)."""
+    chunks = st["life_launches"] // (2 if adjoint else 1)
+    return (st["peel_ms"] > 0 if adjoint else not tally) and st["packages"] >= STAGE_ITEMS * chunks
+
+
+def rooflines(st, prec, adjoint, workload, step_ms, level, tally=False):
+    """Roofline records of every kernel of a call (per launch); the stages of
+    a chunk are one record, their kernels named.  tally: the call had an
+    absorbed tally."""
     res = {}
     for name, (alg, x, launches, ms) in kernel_work(st, prec, adjoint).items():
         if launches == 0 or ms <= 0:
             continue
         key = "%s_%s" % (name, "adjoint" if adjoint else "forward") if name != "peel_deposit" else name
+        stages = name == "life" and in_stages(st, adjoint, tally)
+        if stages:
+            key = "stages_adjoint" if adjoint else "stages_forward"
         launch_s = ms / 1e3 / launches
         achieved = alg / launches / launch_s / 1e9
         traffic = traffic_for(workload, key)
-        r = {"kernel": KERNELS[key], "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        if stages and adjoint:
+            kernel = "in turn: the stages of the first replay (k_emit, k_count, k_move, k_leg, k_event, k_tail), " + \
+                KERNELS["life_adjoint"]
+        elif stages:
+            kernel = "stages of a chunk: " + ", ".join(KERNELS[k] for k in STAGES)
+        else:
+            kernel = KERNELS[key]
+        r = {"kernel": kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
              "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "launch_ms": launch_s * 1e3,
              "launches_per_step": launches, "step_share": ms / step_ms,
              "crossings_per_s": x / (ms / 1e3), "algorithmic_bytes_per_launch": alg / launches,
@@ -334,7 +375,7 @@ def spiral_step(B, W, dev, steps):
     n_pkg = prob["n_packages"]
     fsum, bsum = summary(fw, n_pkg), summary(bw, n_pkg)
     level = "MALL: the 16 MiB grid and 32 MiB tally fit in the 256 MB MALL behind the 4 MB L2 of each XCD"
-    roof = rooflines(fw[-1], 1, False, "spiral", ms_step, level)
+    roof = rooflines(fw[-1], 1, False, "spiral", ms_step, level, tally=True)
     roof.update(rooflines(bw[-1], 1, True, "spiral", ms_step, level))
     st_f = fw[-1]
     out = {"workload": "edge_on_spiral_256x256x64: exp-disk stars in exp-disk dust (face-on tau_V 1), albedo 0.6, "
