@@ -56,12 +56,18 @@
  *    forward's absorbed tally takes up to twice the cells of the grid per
  *    wavelength: its cell units are padded to a power of two), the
  *    adjoint's event scratch, the peel-ray queue and the lists of a run in
- *    stages.  The library keeps such blocks for later calls, at most 64 GiB
- *    and a quarter of a device's memory, and gives them back when they go
- *    unused, when less than half of the memory is free, or on
- *    mcrt_release_workspaces.  Calls may run on several streams and threads:
- *    a block serves one call at a time.  Under stream capture blocks are
- *    neither kept nor reused.
+ *    stages.  The library keeps such blocks for later calls, on each device
+ *    at most 16 of them and the smaller of 64 GiB and a quarter of the
+ *    device's memory.  They go back only at the end of a later call of the
+ *    library that returns a block: those that 32 calls have not used (on any
+ *    device), and all of the call's device when less than half of its memory
+ *    is free; when an allocation of the library fails; and with
+ *    mcrt_release_workspaces.  A program that stops calling the library, or
+ *    whose own allocation fails between two calls, calls that itself;
+ *    mcrt_kept_bytes says how much it would give back.  Calls may run on
+ *    several streams and threads: a block serves one call at a time.  Under
+ *    stream capture blocks are neither kept nor reused; beside a stream that
+ *    is being captured, calls that do not wait leave the capture alone.
  *  - Errors: 0 on success; MCRT_EINVAL for invalid arguments (nothing is
  *    launched), MCRT_EOVERFLOW when a segment buffer was too small,
  *    MCRT_EHIP for a HIP runtime error.  mcrt_last_error() returns a message
@@ -205,7 +211,8 @@ typedef struct {
  * lanes of a wavefront wait before the wavefront processes events (library
  * choice: 32 in the forward run -- 24 when the densities exceed 256 MiB and
  * are walked from HBM -- and 32 and 48 in the adjoint's two replays of each
- * package; a value set here applies to every launch); and the
+ * package, 48 for the walks of a run in stages; a value set here applies to
+ * every launch); and the
  * brick of the library's internal cell layout, MCRT_BRICK(lx, ly, lz) for
  * bricks of 2^lx x 2^ly x 2^lz cells (each log2 in [0, 7], at most 2^10
  * cells).  The default brick fills one 128-byte cache line with the most
@@ -290,10 +297,11 @@ uint64_t mcrt_tape_bytes(const mcrt_optics *optics, int n_det, const mcrt_opts *
  * and its deposit walk when it has one), d_queue the part of deposits made
  * by those deposit walks, which sum them on chip before they reach the
  * tally.  Durations on the stream from HIP events: kernel_ms all kernels of
- * the call, life_ms the life-cycle kernel, queue_ms the sort and the walks
+ * the call, life_ms the life-cycle kernel (in a run in stages all kernels of
+ * the stages), queue_ms the sort and the walks
  * of the peel-ray queue.  life_launches counts the life-cycle kernel's
- * launches (the call runs its packages in chunks; the adjoint launches the
- * kernel twice per chunk).  life_ms is the sum over those launches; queue_ms
+ * launches, a chunk's stages as one (the call runs its packages in chunks;
+ * the adjoint launches the kernel twice per chunk).  life_ms is the sum over those launches; queue_ms
  * = sort_ms (the peel-ray sort) + peel_ms (the queue's optical-depth walks)
  * + dep_ms (the adjoint's deposit walks), each summed over the chunks.
  * With MCRT_ATTACHED: x_path counts the forward sweep's path walks and the

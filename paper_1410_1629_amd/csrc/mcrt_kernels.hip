@@ -6,8 +6,9 @@
 // Sect. 2.1-2.3 (multiple anisotropic scattering; cells of constant
 // properties; geometries; frames; optical properties).
 //
-// Execution model.  One package per lane (mcrt_lane.hpp holds the per-lane
-// state machine and the walk step).  The life-cycle kernel is persistent:
+// Execution model.  Runs without a tally of 2^20 packages and more go through
+// their life cycle in stages (mcrt_stage.hpp), everything else one package per
+// lane (mcrt_lane.hpp holds the per-lane state machine and the walk step).  The life-cycle kernel is persistent:
 // every state that needs a walk through the grid sets up a ray, and all rays,
 // whatever they are for (peel-off, pass-1 path, pass-2 locate, adjoint
 // deposit), advance together in one loop, one cell crossing per iteration,
@@ -529,7 +530,7 @@ struct PkgFeed {
 // spiral that model gives 5.6 ps per crossing for packages in any order, and
 // the first order's legs take 5.7.  In order of place a third of the misses
 // go.  Forward life cycle, lane machine -> stages: spiral (1e7 packages, no
-// tally) 51.4 -> 28.6 ms, clumpy 512^3 disk (4e7) 519 -> 318 ms.
+// tally) 52.4 -> 30.0 ms, clumpy 512^3 disk (4e7) 533 -> 323 ms.
 template <typename R, int GK, bool LUT>
 __global__ void __launch_bounds__(kBlock) k_leg(const StageParams S) {
   const unsigned long long count = *S.n_in;
@@ -770,12 +771,15 @@ __global__ void __launch_bounds__(kSortThreads) k_hist(const unsigned* __restric
 }
 
 // Runs of one first key at least this long skip the second level: its one
-// workgroup per run would walk such a run alone, some 0.14 us per 256 rays (a
+// workgroup per run would walk such a run alone, some 0.12 us per 256 rays (a
 // point source's emission peel-offs all start at one place, one pixel and
-// one depth: 1e7 rays, 5 ms), so k_scatter places their rays in the first
-// level's order itself.  Shorter runs keep the second level, whose order
-// the peel walks need (the clumpy disk's busiest tiles hold a few 1e5 rays
-// per chunk; with a bound of 65536 its peel walks took 1052 ms, not 478).
+// one depth: sorting 1e7 of them takes 4.6 ms so, 0.33 ms without), so k_scatter
+// places their rays in the first level's order itself.  Shorter runs keep the
+// second level, whose order the peel walks need: the disks' busiest tiles hold
+// 2^19 to 2^21 rays per chunk, and with a bound of 2^19 the spiral's peel walks take
+// 37.7 ms, not 18.2, and the clumpy disk's (4e7 packages) 223, not 149, which is
+// more than the 0.4 ms that 1e6 emission rays would save.  Without a bound
+// the spiral's sort is 0.7 ms shorter and its walks equal.
 // k_hot marks the long runs, one bit per key.
 constexpr unsigned kHotRun = 1u << 21;
 __global__ void __launch_bounds__(kSortThreads) k_hot(const unsigned* __restrict__ starts, int n_keys,
@@ -1807,13 +1811,14 @@ int cell_cdf(const double* cell_lum, int nl, int ncell, double* cum, double* til
 //
 // A kept block is idle memory of one device with an event of its last use.
 // A call takes one that is large enough (and not more than four times as
-// large) if that use is over or was on the same stream handle -- it waits for
-// the event on its stream either way -- so streams that overlapped still do,
-// each with blocks of its own.  Under stream capture nothing is kept or
-// taken.  Kept blocks are bounded (kKeepBytes, a quarter of the device,
-// kKeepBlocks) and go back on the stream that replaces them, when 32 calls
-// have not used them, as soon as less than half of the device's memory is
-// free, when an allocation fails, and with mcrt_release_workspaces.
+// large) if that use is over or was on the same stream -- it waits for the
+// event on its stream either way -- so streams that overlapped still do, each
+// with blocks of its own.  Under stream capture nothing is kept or taken.
+// Kept blocks are bounded (mcrt_blocks.hpp): per device kKeepBlocks and the
+// smaller of kKeepBytes and a quarter of its memory.  They go back at the end of
+// a call that returns a block -- those that kKeepCalls calls have not used, and
+// all of the device's when less than half of its memory is free -- when an
+// allocation fails, and with mcrt_release_workspaces: never between calls.
 BlockStore& block_store() {
   static BlockStore* const s = new BlockStore;  // not destroyed: the runtime may be gone by then
   return *s;
