@@ -1877,13 +1877,23 @@ struct RelaxedCapture {
 };
 
 // The device's free memory, counting the idle blocks where the call may take
-// them or give them back: not where its stream is being recorded.
+// them or give them back: not where its stream is being recorded.  Where little
+// is free beside them they go back first, for a call that took one of them for a
+// smaller need of its own would lack the rest.
 int free_memory(hipStream_t st, size_t* free_b) {
   size_t total_b = 0;
   int dev = 0;
   HIPCHK(hipMemGetInfo(free_b, &total_b));
   HIPCHK(hipGetDevice(&dev));
-  if (!stream_capturing(st)) *free_b += block_store().idle_bytes(dev);
+  if (stream_capturing(st)) return 0;
+  const size_t idle_b = block_store().idle_bytes(dev);
+  *free_b += idle_b;
+  if (idle_b >= kKeepLarge && keep_budget(*free_b - idle_b, total_b) == 0) {
+    const RelaxedCapture relaxed;
+    Block b;
+    while (block_store().drop(dev, b)) free_block(b, dev, st);
+    HIPCHK(hipStreamSynchronize(st));  // the pool gives the memory to the device
+  }
   return 0;
 }
 
