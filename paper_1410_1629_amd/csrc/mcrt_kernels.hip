@@ -2507,7 +2507,14 @@ int life(bool adjoint, const mcrt_grid* grid, const void* rho_dev, const mcrt_op
   const size_t off_aab = off_lums + (optg ? align256(sizeof(double) * pr.lums.size()) : 0);
   const bool aabs = adjoint && adj_abs_dev;  // a loss on the absorbed tally: its adjoint, bricked
   const size_t off_stg = off_aab + (aabs ? align256(sizeof(double) * (size_t)nl * P.G.ncell_pad) : 0);
-  const size_t bytes = off_stg + (staged ? StageBytes(chunk).total() : 0);
+  size_t bytes = off_stg;
+  if (staged) {  // where the rest of the call leaves room for the lists
+    bytes += StageBytes(chunk).total();
+    if (bytes > free_b) {
+      staged = false;
+      bytes = off_stg;
+    }
+  }
 
   block_store().call();
   DeviceBlock blk;

@@ -55,3 +55,18 @@ def test_a_kept_block_is_not_spent_on_less_than_the_run_needs():
     assert beside["packages"] == alone["packages"] == 30_000_000
     # which rays a full queue leaves out depends on their order
     assert abs(beside["x_queue"] - alone["x_queue"]) <= 0.02 * alone["x_queue"]
+
+
+def test_a_run_without_room_for_the_stages_goes_without():
+    """A grid that fills nine tenths of what is free leaves no room for the package lists of a run in stages."""
+    import torch
+    from paper_1410_1629_amd import binding as B
+    from paper_1410_1629_amd import workloads as W
+    n = 3_700_000  # their lists take 0.56 GB, of the 0.4 GB beside the densities
+    p = dict(W.cube(n_packages=n, precision=0), n=(800, 800, 800), flags=3)
+    rho = torch.ones(800 ** 3, dtype=torch.float64, device="cuda")  # 4.1 GB, and as much for the library's copy
+    images = torch.empty(B.image_shape(p), dtype=torch.float64, device="cuda")
+    held = _hold(4_500_000_000)
+    st = B.run_photons(p, rho, images, peel_queue=100000)
+    del held
+    assert st["packages"] == n and float(images.sum()) > 0.0
