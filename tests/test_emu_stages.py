@@ -128,6 +128,25 @@ def test_a_full_queue_is_walked_by_the_events(E, W, cap):
     assert _rel(img1, img0) < 1e-11 and _rel(g1, g0) < 1e-10
 
 
+@pytest.mark.parametrize("more", [dict(flags=1), dict(flags=2), dict(flags=0), dict(first_package=(1 << 33) + 5),
+                                  dict(max_scatter=1), dict(max_scatter=2, w_min=0.0), dict(w_min=0.5),
+                                  dict(albedo=[1.0, 0.0, 0.3], g=[0.0, 0.9, -0.9], max_scatter=30)])
+def test_run_options(E, W, more):
+    """Peel-off at emission or scattering alone or not at all, packages of a later range, ends by count and weight."""
+    p = _problem(W, "lambdas", 0, n_pkg=400, **more)
+    p["flags"] = p["flags"] | W.FLAG_SPLIT if p["flags"] & 3 else 0
+    E.set_stages(0)
+    img0, _, st0 = E.run(p)
+    E.set_stages(1, 12)
+    img1, _, st1 = E.run(p)
+    for k in COUNTS:
+        assert st1[k] == st0[k], k
+    for k in ("absorbed", "escaped", "truncated"):
+        assert abs(st1[k] - st0[k]) <= 1e-11 * st0["emitted"], k
+    assert np.abs(img1 - img0).sum() <= 1e-11 * img0.sum()
+    assert (img0.sum() > 0.0) == bool(p["flags"] & 3)
+
+
 @pytest.mark.parametrize("max_chunk", [64, 257])
 def test_chunks(E, W, max_chunk):
     _same(*_both(E, _problem(W, "lambdas", 1), (1, 12), tape=True, max_chunk=max_chunk))
