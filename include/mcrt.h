@@ -488,8 +488,8 @@ int backward(const mcrt_grid *grid, const void *rho_dev, const mcrt_optics *opti
  * emission_dev [n_lambda][cell] receives
  *   L_m * kappa_abs[i] B(lambda[i], T_m) dlambda[i]
  *       / sum_j kappa_abs[j] B(lambda[j], T_m) dlambda[j],
- * so every cell re-emits exactly what it absorbed (nothing where that sum
- * underflows to 0).  lambda (um), dlambda
+ * so every cell re-emits what it absorbed, to within n_lambda + 2 units of
+ * 2^-53 (nothing where that sum underflows to 0).  lambda (um), dlambda
  * (bin widths, um), kappa_abs (absorption opacity per unit density): host
  * arrays [n_lambda], > 0; emissivity > 0 sets the temperature scale only.
  * rho_dev: densities [cell] (double, or float with MCRT_PREC_FP32);

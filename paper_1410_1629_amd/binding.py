@@ -180,7 +180,9 @@ def _check(rc):
 
 def release_workspaces():
     """mcrt_release_workspaces: gives back the device memory that the library
-    keeps between calls."""
+    keeps between calls (at most 64 GiB and a quarter of the device).  It gives
+    some back by itself, but only in later calls: a program that is about to
+    fill the device, or is done with the library, calls this."""
     _check(load().mcrt_release_workspaces())
 
 
