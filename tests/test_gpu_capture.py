@@ -5,6 +5,7 @@ Device memory that calls on a third stream left behind is there to be taken,
 so the calls look at its state."""
 import ctypes as C
 
+import hiprt
 import numpy as np
 import pytest
 
@@ -39,7 +40,7 @@ def test_a_recording_goes_on_beside_a_call(name):
     import torch
     from paper_1410_1629_amd import binding as B
     from paper_1410_1629_amd import workloads as W
-    hip = C.CDLL("libamdhip64.so")
+    hip = hiprt.load()
     calls, keep = _calls(B, W)
     call, out = calls[name]
     recorded, beside, other = (torch.cuda.Stream() for _ in range(3))

@@ -1,6 +1,7 @@
 """Kept device memory goes back without being asked for: after calls that do not
 use it, and at the end of any call, small ones too, that finds less than half
 of the device's memory free."""
+import hiprt
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -74,7 +75,7 @@ def test_a_recorded_run_plans_without_the_kept_memory():
     import torch
     from paper_1410_1629_amd import binding as B
     from paper_1410_1629_amd import workloads as W
-    hip = C.CDLL("libamdhip64.so")
+    hip = hiprt.load()
     stream = torch.cuda.Stream()
     p = W.cube(n_packages=30_000_000, precision=1)
     p["flags"] = 3
